@@ -895,7 +895,7 @@ inline hipError_t launch_cfg(GemmArgs g, hipStream_t s) {
 }
 
 // Tile configurations: workgroup tile, wave grid (wave tile), K-steps in
-// flight, LDS.  readme_set_gemm_tile() forces one process-wide.
+// flight, LDS.  readme_set_gemm_tile() forces one for the calling thread.
 enum TileCfg {
     TILE_AUTO = 0,
     TILE_256x256 = 1,      // 2x4 waves of 128x64, 2 stages, 128 KB
@@ -935,12 +935,11 @@ enum TileCfg {
     TILE_BD_32x128_W4 = 27,     // 6 K-steps in flight
     TILE_BD_32x128_W4_S8 = 28,  // 8 K-steps in flight
     TILE_BD_32x128_W4_S4 = 29,  // 4 K-steps in flight
-    // Tiles of several heights in one launch, eight waves (two per SIMD) of
-    // one 32-column weight group each (256 columns; gate/up paired across
-    // waves):
-    TILE_MIX8_256 = 30,  // 256 (2 K-steps), 128, 64 rows (4 K-steps)
-    TILE_MIX8_192 = 31,  // 192 (3 K-steps), 128, 64 rows (4 K-steps)
-    TILE_LAST = TILE_MIX8_192,
+    // Tiles of several heights in one launch, eight waves (two per SIMD) in
+    // two opposite phases, both operands in LDS (bf16; see gemm_pp.hpp):
+    TILE_PP_256 = 30,  // 256, 128, 64 rows
+    TILE_PP_128 = 31,  // 128, 64 rows
+    TILE_LAST = TILE_PP_128,
 };
 
 // Launches one tile configuration (instantiated per element type and

@@ -7,9 +7,8 @@
 // and its remainder r goes to the class of the smallest height that holds
 // it (B1 >= r > B2 -> class 1, and so on); a remainder above B1 takes one
 // more B0 tile.  All classes are register-streamed tiles (BdTile) of 256
-// output columns with the same waves -- four waves of two 32-column groups,
-// or eight waves (two per SIMD) of one group each -- so the launch runs one
-// kernel whose workgroups pick their class's tile routine.
+// output columns with the same four waves of two 32-column groups, so the
+// launch runs one kernel whose workgroups pick their class's tile routine.
 //
 // Order.  The blocks of class 0 come first, then class 1, and so on, so the
 // dispatcher starts the longest tiles first and fills the tail of the launch
@@ -121,11 +120,10 @@ __device__ __forceinline__ bool mix_locate(const GemmArgs& g, int c, int L, Tile
     return false;
 }
 
-// NW waves of TN 32-column groups each (NW * TN = 8: 256 columns).
-template <int B0, int B1, int B2, int B3, int S0, int S1, int S2, int S3, int EPI, int NW,
-          int TN>
+// Four waves of two 32-column groups each: 256 columns.
+template <int B0, int B1, int B2, int B3, int S0, int S1, int S2, int S3, int EPI>
 struct MixKernel {
-    static_assert(NW * TN == 8, "256 output columns per tile");
+    static constexpr int NW = 4, TN = 2;
     using Mix = MixRows<B0, B1, B2, B3>;
     // Classes that are absent reuse class 0's routine type (never run).
     using T0 = BdTile<B0, NW, TN, S0, false, EPI>;
@@ -137,13 +135,9 @@ struct MixKernel {
         cmax(cmax(T0::LDS_SLOTS, T1::LDS_SLOTS), cmax(T2::LDS_SLOTS, T3::LDS_SLOTS));
 };
 
-// Eight-wave tiles are compiled for two waves per SIMD (at most 256
-// registers per lane, accumulators included).
-template <int B0, int B1, int B2, int B3, int S0, int S1, int S2, int S3, int EPI, int NW,
-          int TN>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW > 4 ? 2 : 1)))
-void k_grouped_gemm_mix(GemmArgs g) {
-    using K = MixKernel<B0, B1, B2, B3, S0, S1, S2, S3, EPI, NW, TN>;
+template <int B0, int B1, int B2, int B3, int S0, int S1, int S2, int S3, int EPI>
+__global__ __launch_bounds__(256) void k_grouped_gemm_mix(GemmArgs g) {
+    using K = MixKernel<B0, B1, B2, B3, S0, S1, S2, S3, EPI>;
     using Mix = typename K::Mix;
     __shared__ u32x4 lds[K::SLOTS];
     __shared__ int32_t crow[B0];
@@ -169,12 +163,11 @@ void k_grouped_gemm_mix(GemmArgs g) {
     }
 }
 
-// Host: block ranges per class from upper bounds of their tile counts.
-template <int B0, int B1, int B2, int B3, int S0, int S1, int S2, int S3, int EPI, int NW,
-          int TN>
-inline hipError_t launch_mix(GemmArgs g, hipStream_t s) {
-    using Mix = MixRows<B0, B1, B2, B3>;
-    g.n_tiles = (int)ceil_div(g.N, NW * TN * 32);
+// Host: block ranges per class from upper bounds of their tile counts, for
+// tiles of BN columns; g.mix_start[4] is the grid (0: nothing to do).
+template <class Mix>
+inline hipError_t mix_ranges(GemmArgs& g, int BN) {
+    g.n_tiles = (int)ceil_div(g.N, BN);
     const int64_t groups = (int64_t)g.E + g.shared_groups;
     int64_t start = 0;
     for (int c = 0; c < 4; ++c) {
@@ -183,43 +176,48 @@ inline hipError_t launch_mix(GemmArgs g, hipStream_t s) {
         // Class 0: at most ceil(rows / B0) per group; a smaller class: at
         // most one remainder tile per group, and each holds more than the
         // next smaller height's rows.
-        int64_t mt = m_tiles_bound(g, B0);
+        int64_t mt = m_tiles_bound(g, Mix::height(0));
         if (c > 0) {
             const int lower = c + 1 < Mix::NC ? Mix::height(c + 1) : 0;
             const int64_t rows = g.T * (1 + (int64_t)g.shared_groups);
             mt = groups < rows / (lower + 1) ? groups : rows / (lower + 1);
         }
         start += round_up(mt * g.n_tiles, 8);
+        if (start > 0x7fffffffLL) return hipErrorInvalidValue;
     }
     g.mix_start[4] = (int)start;
-    if (start == 0) return hipSuccess;
-    if (start > 0x7fffffffLL) return hipErrorInvalidValue;
-    k_grouped_gemm_mix<B0, B1, B2, B3, S0, S1, S2, S3, EPI, NW, TN>
-        <<<dim3((unsigned)start), dim3(NW * 64), 0, s>>>(g);
+    return hipSuccess;
+}
+
+template <int B0, int B1, int B2, int B3, int S0, int S1, int S2, int S3, int EPI>
+inline hipError_t launch_mix(GemmArgs g, hipStream_t s) {
+    const hipError_t err = mix_ranges<MixRows<B0, B1, B2, B3>>(g, 256);
+    if (err != hipSuccess || g.mix_start[4] == 0) return err;
+    k_grouped_gemm_mix<B0, B1, B2, B3, S0, S1, S2, S3, EPI>
+        <<<dim3((unsigned)g.mix_start[4]), dim3(256), 0, s>>>(g);
     return hipGetLastError();
 }
 
 template <int EPI>
 hipError_t launch_mix_tile(int tile, GemmArgs g, hipStream_t s) {
     switch (tile) {
-        case TILE_MIX_256: return launch_mix<256, 128, 64, 32, 2, 4, 4, 4, EPI, 4, 2>(g, s);
-        case TILE_MIX_192: return launch_mix<192, 128, 64, 32, 2, 4, 4, 4, EPI, 4, 2>(g, s);
-        case TILE_MIX_128: return launch_mix<128, 64, 32, 0, 4, 4, 4, 4, EPI, 4, 2>(g, s);
-        // Eight waves: a 32-row class would give a wave less than one
-        // 8-row activation load, so remainders of up to 64 rows take 64.
-        case TILE_MIX8_256: return launch_mix<256, 128, 64, 0, 2, 4, 4, 4, EPI, 8, 1>(g, s);
-        case TILE_MIX8_192: return launch_mix<192, 128, 64, 0, 3, 4, 4, 4, EPI, 8, 1>(g, s);
+        case TILE_MIX_256: return launch_mix<256, 128, 64, 32, 2, 4, 4, 4, EPI>(g, s);
+        case TILE_MIX_192: return launch_mix<192, 128, 64, 32, 2, 4, 4, 4, EPI>(g, s);
+        case TILE_MIX_128: return launch_mix<128, 64, 32, 0, 4, 4, 4, 4, EPI>(g, s);
         default: return hipErrorInvalidValue;
     }
 }
 
-inline bool is_mix_tile(int tile) {
-    return (tile >= TILE_MIX_256 && tile <= TILE_MIX_128) || tile == TILE_MIX8_256 ||
-           tile == TILE_MIX8_192;
-}
+inline bool is_mix_tile(int tile) { return tile >= TILE_MIX_256 && tile <= TILE_MIX_128; }
 
 hipError_t launch_mix_bf16_gate_up(int tile, GemmArgs g, hipStream_t s);
 hipError_t launch_mix_bf16_store(int tile, GemmArgs g, hipStream_t s);
 hipError_t launch_mix_bf16_resid(int tile, GemmArgs g, hipStream_t s);
+
+// gemm_pp.hpp
+inline bool is_pp_tile(int tile) { return tile == TILE_PP_256 || tile == TILE_PP_128; }
+hipError_t launch_pp_bf16_gate_up(int tile, GemmArgs g, hipStream_t s);
+hipError_t launch_pp_bf16_store(int tile, GemmArgs g, hipStream_t s);
+hipError_t launch_pp_bf16_resid(int tile, GemmArgs g, hipStream_t s);
 
 }  // namespace readme

@@ -705,7 +705,7 @@ hipError_t launch_attention(int64_t T, int H, int32_t R, const int32_t* pos, con
 // 27.4 us with the eight-wave 256-row tiles, o and down (N = D) 15.6 -
 // 16.3 us with 64 x 256 four-wave tiles against 28 us automatic, gate/up
 // (N = 2F) 18.2 us with 128 x 256 LDS tiles against 28.6.
-constexpr int kTileQkv = 30;     // TILE_MIX8_256
+constexpr int kTileQkv = 30;     // TILE_PP_256
 constexpr int kTileNarrow = 13;  // TILE_BD_64x256
 constexpr int kTileGateUp = 4;   // TILE_128x256
 
