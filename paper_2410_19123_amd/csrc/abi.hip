@@ -498,10 +498,17 @@ readme_status stack_impl(int64_t T, int64_t d, int32_t E, int64_t I, int32_t L,
     uint16_t* xn = reinterpret_cast<uint16_t*>(workspace);
     uint16_t* h = xn + T * d;
     for (int32_t l = 0; l < L; ++l) {
-        hipError_t err = launch_rms_to_bf16(T, d, x_resid_grouped, offsets, E, rms_eps, xn, s);
-        if (err != hipSuccess) return README_ERR_HIP;
+        hipError_t err = hipSuccess;
         GemmArgs gu = gate_up_args(README_BF16, T, d, E, I, xn, offsets, packed_per_layer[l], h);
         gu.m_tiles32 = m32;
+        gu.rms_in = gate_up_takes_norm(gu);
+        if (gu.rms_in) {
+            gu.A = x_resid_grouped;
+            gu.rms_eps = rms_eps;
+        } else {
+            err = launch_rms_to_bf16(T, d, x_resid_grouped, offsets, E, rms_eps, xn, s);
+        }
+        if (err != hipSuccess) return README_ERR_HIP;
         err = launch_grouped_gemm(false, EPI_GATE_UP_SILU, gu, s);
         if (err != hipSuccess) return README_ERR_HIP;
         GemmArgs dn = down_args(README_BF16, T, d, E, I, h, offsets, packed_per_layer[l],

@@ -1,8 +1,10 @@
 // Host side of the grouped GEMM: tile choice and dispatch.  The kernels are
 // in gemm_kernels.hpp, instantiated in gemm_f32.hip and gemm_bf16_*.hip.
 #include <limits.h>
+#include <math.h>
 
 #include "gemm_pp.hpp"
+#include "gemm_decode.hpp"
 
 namespace readme {
 
@@ -37,22 +39,54 @@ static float tile_cost(int height, const GemmArgs& g) {
     const float nk = (float)g.K / 64.0f;
     const int64_t groups = g.E + g.shared_groups;
     const int64_t rows = g.T * (1 + g.shared_groups);
-    const int64_t n_n = ceil_div(g.N, height == 32 ? 128 : 256);
-    const float tiles =
-        (height == 32 && g.m_tiles32 > 0 ? (float)g.m_tiles32
-                                         : (float)rows / height + 0.5f * groups) * n_n / 256.0f;
-    if (height == 32) {  // several workgroups per CU: no rounds
-        const float t = 0.42f * tiles;
-        return 3.0f + nk * (t > 0.5f ? t : 0.5f);
-    }
+    const float tiles = ((float)rows / height + 0.5f * groups) * ceil_div(g.N, 256) / 256.0f;
     const float rounds = tiles <= 1.0f ? 1.0f : tiles + 0.4f;
     if (height == 64) return rounds * (5.0f + 0.75f * nk);
     if (height == 128) return rounds * (5.6f + 0.92f * nk);
     return rounds * (6.4f + 1.22f * nk);
 }
 
-// Tile of a launch.  bf16: the cheapest by tile_cost of 32 x 128 (four waves
-// each streaming one weight group), 64 x 256 (four waves), and the two
+// Whether the launch is a decode launch: by its sizes alone, never by the
+// counts, since the summation order follows from it.
+static bool decode_launch(const GemmArgs& g) {
+    const float tiles =
+        ((float)(g.T * (1 + g.shared_groups)) / 32.0f + 0.5f * (g.E + g.shared_groups)) *
+        ceil_div(g.N, 128) / 256.0f;
+    const float t = 0.42f * tiles;
+    const float cost = 3.0f + (float)g.K / 64.0f * (t > 0.5f ? t : 0.5f);
+    return cost <= tile_cost(64, g) && cost <= tile_cost(128, g) && cost <= tile_cost(256, g);
+}
+
+// Decode: the estimated 32-row tiles of the launch.  Without the caller's
+// counts, the experts that T tokens of a uniform load reach, and half a tile
+// of padding for each expert when they fill tiles.
+static float decode_m_tiles(const GemmArgs& g) {
+    if (g.m_tiles32 > 0) return (float)g.m_tiles32;
+    const float T = (float)g.T, E = (float)g.E;
+    const float active = E * (1.0f - powf(1.0f - 1.0f / E, T));
+    const float full = T / 32.0f + 0.5f * active;
+    const float m = (active > full ? active : full) + g.shared_groups * ceilf(T / 32.0f);
+    const float bound = (float)m_tiles_bound(g, 32);
+    return m < bound ? m : bound;
+}
+
+// Time (us) of a decode launch with m 32-row tiles on the workgroup of `cols`
+// columns: 256 at a time, each CU moving about 46 bytes per ns of weights and
+// activation rows (16 rows per 16-token tile, all of them by every
+// workgroup).  128 columns: the tile whose waves share the rows through LDS;
+// more than one fits a CU, so a second round costs less than a whole one.
+static float decode_cost(int cols, const GemmArgs& g, float m) {
+    const float n = m * (float)ceil_div(g.N, (int64_t)cols) / 256.0f;
+    const float rows = cols == 128 || (float)g.T > 16.0f * m ? 32.0f : 16.0f;
+    const float bytes = 2.0f * (float)g.K * ((float)cols + rows);
+    const float rounds = n <= 1.0f ? 1.0f : cols == 128 ? n + 0.3f : ceilf(n);
+    return rounds * ((cols == 128 ? 1.5f : 2.5f) + bytes / 46000.0f);
+}
+
+// Tile of a launch.  bf16, by the estimates above.  Decode (the 32 x 128 tile
+// would be the cheapest of the fixed heights, whatever the split over
+// experts): the kernels of one summation order (gemm_decode.hpp), among which
+// the caller's counts may choose.  Else 64 x 256 (four waves) or one of the
 // mixed-height launches of gemm_pp.hpp, whose tall tiles are the fastest per
 // flop.
 static int tile_by_shape(bool f32, bool gate_up, const GemmArgs& g) {
@@ -64,23 +98,28 @@ static int tile_by_shape(bool f32, bool gate_up, const GemmArgs& g) {
         if (per_expert >= (gate_up ? 768 : 192)) return TILE_256x256;
         return per_expert >= 96 && !gate_up ? TILE_128x256 : TILE_32x128;
     }
-    constexpr int kHeights = 4;
-    const int height[kHeights] = {32, 64, 128, 256};
-    const int tile[kHeights] = {TILE_BD_32x128_W4, TILE_BD_64x256, TILE_PP_128, TILE_PP_256};
-    int best = 0;
-    float cost = tile_cost(height[0], g);
-    for (int i = 1; i < kHeights; ++i) {
-        const float c = tile_cost(height[i], g);
-        if (c < cost) {
-            cost = c;
-            best = i;
+    const float c64 = tile_cost(64, g), c128 = tile_cost(128, g), c256 = tile_cost(256, g);
+    if (decode_launch(g)) {
+        const float m = decode_m_tiles(g);
+        const int tile[4] = {TILE_DECODE_128, TILE_SKINNY_64, TILE_SKINNY_32, TILE_SKINNY_16};
+        int best = 0;
+        float cost = decode_cost(128, g, m);
+        for (int i = 1; i < 4; ++i) {
+            const float c = decode_cost(128 >> i, g, m);
+            if (c < 0.97f * cost) {
+                cost = c;
+                best = i;
+            }
         }
+        return tile[best];
     }
-    // Few 32-row tiles, known from the caller's counts (tokens concentrated
-    // on few experts): 64 columns, so that twice as many workgroups stream.
-    if (best == 0 && g.m_tiles32 > 0 && (int64_t)g.m_tiles32 * ceil_div(g.N, 128) < 128)
-        return TILE_BD_32x64;
-    return tile[best];
+    if (c64 <= c128 && c64 <= c256) return TILE_BD_64x256;
+    return c128 <= c256 ? TILE_PP_128 : TILE_PP_256;
+}
+
+bool gate_up_takes_norm(GemmArgs g) {
+    if (forced_tile() > 0 || g.T > kNormRows || g.K > kNormWidth) return false;
+    return decode_launch(g);
 }
 
 hipError_t launch_grouped_gemm(bool f32, int epi, GemmArgs g, hipStream_t s) {
@@ -91,8 +130,15 @@ hipError_t launch_grouped_gemm(bool f32, int epi, GemmArgs g, hipStream_t s) {
     if (g.K >= (int64_t)32 << 16) return hipErrorInvalidValue;
     if (g.k_segs > 1 && epi != EPI_STORE) return hipErrorInvalidValue;  // segments: down only
     int tile = tile_by_shape(f32, epi == EPI_GATE_UP_SILU, g);
-    // gemm_pp.hpp keeps activation offsets in 32 bits of 16 bytes each.
+    if (g.rms_in) {  // gate_up_takes_norm: a weight stream, of at most 32 columns
+        if (tile != TILE_SKINNY_16) tile = TILE_SKINNY_32;
+        return launch_decode_bf16(tile, epi, g, s);
+    }
+    // gemm_pp.hpp and gemm_decode.hpp keep activation offsets in 32 bits of 16
+    // bytes each.
     if (is_pp_tile(tile) && g.T * (g.lda >> 3) > INT32_MAX) tile = TILE_MIX_256;
+    if (tile >= TILE_SKINNY_16 && g.T * (g.lda >> 3) > INT32_MAX) tile = TILE_DECODE_128;
+    if (!f32 && tile >= TILE_SKINNY_16) return launch_decode_bf16(tile, epi, g, s);
     if (!f32 && is_pp_tile(tile)) {
         if (epi == EPI_GATE_UP_SILU) return launch_pp_bf16_gate_up(tile, g, s);
         if (epi == EPI_RESID_ADD) return launch_pp_bf16_resid(tile, g, s);

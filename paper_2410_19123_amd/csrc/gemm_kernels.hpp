@@ -87,6 +87,14 @@ __device__ __forceinline__ void block_barrier() {
 // LDS slot of logical 16-byte chunk c of tile row r (an XOR: its own inverse).
 __device__ __forceinline__ int swz(int c, int r) { return c ^ ((r >> 1) & 7); }
 
+// The value, in its one register at this point of the program: a lane offset
+// used in the K loop is not widened to 64 bits ahead of it (two registers for
+// the whole loop).
+__device__ __forceinline__ uint32_t keep32(uint32_t v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
 // Instruction schedule of one K-step's fragment reads and MFMAs.  Left to
 // itself the scheduler reuses one set of fragment registers and waits on
 // every LDS read right before the MFMAs that need it; these group barriers
@@ -939,7 +947,12 @@ enum TileCfg {
     // two opposite phases, both operands in LDS (bf16; see gemm_pp.hpp):
     TILE_PP_256 = 30,  // 256, 128, 64 rows
     TILE_PP_128 = 31,  // 128, 64 rows
-    TILE_LAST = TILE_PP_128,
+    TILE_LAST = TILE_PP_128,  // the last that can be forced
+    // Weight streams for few tokens per expert (bf16; see gemm_decode.hpp).
+    TILE_SKINNY_16 = 32,  // 32 rows x 16 columns
+    TILE_SKINNY_32 = 33,  // 32 rows x 32 columns
+    TILE_SKINNY_64 = 34,  // 32 rows x 64 columns
+    TILE_DECODE_128 = 35,  // 32 rows x 128 columns
 };
 
 // Launches one tile configuration (instantiated per element type and
@@ -988,5 +1001,7 @@ hipError_t launch_tile_f32_store(int tile, GemmArgs g, hipStream_t s);
 hipError_t launch_tile_bf16_gate_up(int tile, GemmArgs g, hipStream_t s);
 hipError_t launch_tile_bf16_store(int tile, GemmArgs g, hipStream_t s);
 hipError_t launch_tile_bf16_resid(int tile, GemmArgs g, hipStream_t s);
+
+hipError_t launch_decode_bf16(int tile, int epi, GemmArgs g, hipStream_t s);
 
 }  // namespace readme

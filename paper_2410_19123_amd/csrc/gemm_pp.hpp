@@ -70,14 +70,6 @@ __device__ __forceinline__ void pp_barrier() {
     __builtin_amdgcn_sched_barrier(0);
 }
 
-// The value, in its one register at this point of the program: a lane offset
-// used in the K loop is not widened to 64 bits ahead of it (two registers for
-// the whole loop).
-__device__ __forceinline__ uint32_t pp_keep32(uint32_t v) {
-    asm volatile("" : "+v"(v));
-    return v;
-}
-
 // The LDS parts, one __shared__ array each: the compiler tells distinct
 // arrays apart, so a read of one does not wait for transfers into another.
 struct PpLds {
@@ -177,14 +169,14 @@ struct PpTile {
 #pragma unroll
             for (int i = 0; i < AI; ++i)
                 dma16(reinterpret_cast<const char*>(g.A) + (int64_t)kt * 128 +
-                          (uint64_t)pp_keep32(a_src[p][i]) * 16,
+                          (uint64_t)keep32(a_src[p][i]) * 16,
                       L.p[a_part(b, p)] + (wave + 8 * i) * 64);
         };
         auto dma_b = [&](auto bc, auto hc, const char* bs) {
             constexpr int b = decltype(bc)::value, h = decltype(hc)::value;
 #pragma unroll
             for (int i = 0; i < BI; ++i)
-                dma16(bs + b_off[h][i] + pp_keep32(b_lane), L.p[b_part(b, h)] + (wave + 8 * i) * 64);
+                dma16(bs + b_off[h][i] + keep32(b_lane), L.p[b_part(b, h)] + (wave + 8 * i) * 64);
         };
         using I0 = std::integral_constant<int, 0>;
         using I1 = std::integral_constant<int, 1>;

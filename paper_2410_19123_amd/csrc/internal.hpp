@@ -50,6 +50,10 @@ struct GemmArgs {
     // tile > 0: this launch's tile configuration (a caller that measured its
     // own shapes); the calling thread's override still takes precedence.
     int tile;
+    // rms_in (gate/up of few tokens): A is the fp32 residual, normalised
+    // (eps rms_eps) on the way in.
+    bool rms_in;
+    float rms_eps;
     int n_tiles, m_tiles_max; // filled by the launcher
     // Tiles of several heights in one launch: the block range of class c is
     // [mix_start[c], mix_start[c+1]) (filled by the launcher).
@@ -77,6 +81,9 @@ hipError_t launch_pack_slots(readme_dtype dt, int64_t E_all, int64_t e0, int64_t
 hipError_t launch_pack_rows_bf16(int64_t N, int64_t K, int64_t row0, int64_t n,
                                  const void* src, int64_t ld, void* packed, hipStream_t s);
 hipError_t launch_grouped_gemm(bool f32, int epi, GemmArgs g, hipStream_t s);
+// Whether a gate/up launch of these sizes can normalise the fp32 residual
+// itself (rms_in), with the same results as launch_rms_to_bf16 before it.
+bool gate_up_takes_norm(GemmArgs g);
 // Arguments of the two FFN GEMMs over a packed expert buffer (abi.hip).
 GemmArgs gate_up_args(readme_dtype dt, int64_t T, int64_t d, int32_t E, int64_t I,
                       const void* xg, const int32_t* offsets, const void* packed, void* h);
