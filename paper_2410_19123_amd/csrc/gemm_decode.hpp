@@ -334,8 +334,9 @@ inline hipError_t launch_skinny(GemmArgs g, hipStream_t s) {
 // rows and the 16 up rows of the same neurons, which meet in one lane), the
 // token rows shared through LDS.
 template <int EPI>
-__global__ __launch_bounds__(256) void k_decode(GemmArgs args) {
-    constexpr int S = 6;  // K-steps in flight
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
+void k_decode(GemmArgs args) {
+    constexpr int S = 5;  // K-steps in flight: what three waves per SIMD hold
     constexpr bool GU = EPI == EPI_GATE_UP_SILU;
     __shared__ u32x4 lds[2][32 * CPR];
     TileLoc t;
@@ -374,13 +375,6 @@ __global__ __launch_bounds__(256) void k_decode(GemmArgs args) {
     const bool in = l32 < t.rows;
     int64_t crow = t.m0 + (in ? l32 : 0);
     if (g.c_rows) crow = g.c_rows[crow];
-    f32x4 res[4];
-    if constexpr (EPI == EPI_RESID_ADD) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            res[i] = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(g.C) +
-                                                     crow * g.ldc + u * 32 + i * 8 + half * 4);
-    }
     u32x4 aq[S];
     static_for<0, S>([&](auto sc) {
         constexpr int s = decltype(sc)::value;
@@ -427,25 +421,52 @@ __global__ __launch_bounds__(256) void k_decode(GemmArgs args) {
     int kt0 = 0;
     for (; kt0 + S <= nk; kt0 += S)
         static_for<0, S>([&](auto sc) { step(sc, kt0 + decltype(sc)::value); });
+    f32x4 res[4];
+    if constexpr (EPI == EPI_RESID_ADD) {  // arrives during the last K-steps
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            res[i] = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(g.C) +
+                                                     crow * g.ldc + u * 32 + i * 8 + half * 4);
+    }
     static_for<0, S - 1>([&](auto sc) {
         if (kt0 + decltype(sc)::value < nk) step(sc, kt0 + decltype(sc)::value);
     });
     fold();
 
-    if (!in || crow < 0 || crow >= g.T || unit * 32 >= g.N) return;
+    const bool ok = in && crow >= 0 && crow < g.T && unit * 32 < g.N;
+    if (EPI == EPI_RESID_ADD && !ok) return;
+    if constexpr (EPI == EPI_RESID_ADD) {
 #pragma unroll
-    for (int i = 0; i < (GU ? 2 : 4); ++i) {
-        float v[4];
+        for (int i = 0; i < 4; ++i) {
+            const f32x4 o = {res[i][0] + tot[4 * i], res[i][1] + tot[4 * i + 1],
+                             res[i][2] + tot[4 * i + 2], res[i][3] + tot[4 * i + 3]};
+            *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(g.C) + crow * g.ldc + unit * 32 +
+                                      i * 8 + half * 4) = o;
+        }
+    } else {
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-            v[r] = GU ? silu_f32(tot[4 * i + r]) * tot[8 + 4 * i + r] : tot[4 * i + r];
-        const int64_t col = (int64_t)unit * (GU ? 16 : 32) + i * 8 + half * 4;
-        if constexpr (EPI == EPI_RESID_ADD) {
-            const f32x4 o = {res[i][0] + v[0], res[i][1] + v[1], res[i][2] + v[2],
-                             res[i][3] + v[3]};
-            *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(g.C) + crow * g.ldc + col) = o;
-        } else {
-            decode_store4(g, crow, col, v);
+        for (int i = 0; i < (GU ? 2 : 4); i += 2) {
+            // Columns 8i + 4*half .. +3 and 8(i+1) + 4*half .. +3; the other
+            // half's lane of the row holds their neighbours.
+            uint32_t w[2][2];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                float v[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int k = 4 * (i + j) + r;
+                    v[r] = GU ? silu_f32(tot[k]) * tot[(8 + k) & 15] : tot[k];
+                }
+                w[j][0] = (uint32_t)f32_to_bf16(v[0]) | ((uint32_t)f32_to_bf16(v[1]) << 16);
+                w[j][1] = (uint32_t)f32_to_bf16(v[2]) | ((uint32_t)f32_to_bf16(v[3]) << 16);
+            }
+            const auto a = __builtin_amdgcn_permlane32_swap(w[0][0], w[1][0], false, false);
+            const auto b = __builtin_amdgcn_permlane32_swap(w[0][1], w[1][1], false, false);
+            const u32x4 o = {a[0], b[0], a[1], b[1]};
+            const int64_t col = (int64_t)unit * (GU ? 16 : 32) + (i + half) * 8;
+            if (ok)
+                *reinterpret_cast<u32x4*>(reinterpret_cast<uint16_t*>(g.C) + crow * g.ldc + col) =
+                    o;
         }
     }
 }
