@@ -103,4 +103,19 @@ hipError_t launch_combine(bool f32, int64_t T, int64_t d, int K, const void* y_p
 hipError_t launch_rms_to_bf16(int64_t T, int64_t d, const float* x, const int32_t* offsets, int E,
                               float eps, uint16_t* xn, hipStream_t s);
 
+// The router block's two fused kernels (router_fused.hip): D = 512, a padded
+// MLP width of at most kFusedRouterMlp.
+constexpr int kFusedRouterWidth = 512;
+constexpr int kFusedRouterMlp = 1536;
+// Tokens from which the two kernels are the faster form (router_fused.hip).
+inline int64_t fused_router_tokens(int64_t F) { return 1800 + F * 7 / 5; }
+hipError_t launch_router_head(int64_t T, int32_t R, int64_t V, float eps, const int32_t* tokens,
+                              const int32_t* ro, const void* emb, float* x, uint16_t* a,
+                              int32_t* pos, int32_t* offs, const void* wqkv, uint16_t* qkv,
+                              hipStream_t s);
+hipError_t launch_router_tail(int64_t T, int64_t F, int E, float eps, const uint16_t* o,
+                              const void* wo, const void* mlp, const void* gate, const float* bias,
+                              float* x, uint16_t* m, uint16_t* h, uint16_t* f, int32_t* ids,
+                              float* logits, hipStream_t s);
+
 }  // namespace readme

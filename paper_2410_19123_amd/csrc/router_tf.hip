@@ -18,12 +18,13 @@
 // first norm, the MLP's norm, RoPE, causal attention, and the final norm
 // fused with the gate (readme_route's canonical fp32 order).  Nine launches
 // per call (embedding + norm, q|k|v, RoPE, attention, Wo, norm, gate/up, down,
-// norm + gate; the last is two, norm then gate, for D > 2048).
+// norm + gate; the last is two, norm then gate, for D > 2048), or three where
+// D = 512 and the tokens are many: router_fused.hip before and after the
+// attention.
 #include <limits.h>
 #include <math.h>
 
-#include "common.hpp"
-#include "internal.hpp"
+#include "router_common.hpp"
 
 namespace readme {
 
@@ -46,33 +47,6 @@ __device__ __forceinline__ int64_t request_start(int64_t t, const int32_t* __res
     if (p < 0) p = 0;
     if (p > t) p = t;
     return t - p;
-}
-
-// Position of token t in its request: t - ro[r] for the last r with
-// ro[r] <= t (ro = request offsets [R + 1], ro[0] = 0, ro[R] = T).
-__device__ __forceinline__ int32_t position_of(int64_t t, int32_t R,
-                                               const int32_t* __restrict__ ro) {
-    int lo = 0, hi = R;
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (ro[mid] <= t) lo = mid;
-        else hi = mid;
-    }
-    int64_t start = ro[lo];
-    if (start < 0) start = 0;
-    if (start > t) start = t;
-    return (int32_t)(t - start);
-}
-
-// Request offsets staged in LDS for the position search when they fit.
-constexpr int kRoLds = 4096;
-
-// Sum over the wave to lane 0 in a fixed order, then broadcast, so that every
-// lane holds the same fp32 total.
-__device__ __forceinline__ float wave_sum_bcast(float v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_down(v, off, 64);
-    return __shfl(v, 0, 64);
 }
 
 // Embedding and the pre-attention norm, one wave per token (four per
@@ -700,14 +674,16 @@ hipError_t launch_attention(int64_t T, int H, int32_t R, const int32_t* pos, con
     return hipGetLastError();
 }
 
-// Tile configurations (TILE_* of the grouped GEMM) of the block's GEMMs
-// from a sweep of all tiles at 8192 tokens, D = F = 512: q|k|v (N = 3D)
-// 27.4 us with the eight-wave 256-row tiles, o and down (N = D) 15.6 -
-// 16.3 us with 64 x 256 four-wave tiles against 28 us automatic, gate/up
-// (N = 2F) 18.2 us with 128 x 256 LDS tiles against 28.6.
+// Tile configurations (TILE_* of the grouped GEMM) of the block's GEMMs where
+// the fused kernels do not run and T * D is at least 4 M: q|k|v on 256-row
+// tiles, o and down (N = D) on 64 x 256, gate/up on 128 rows.  Below that the
+// automatic choice is the faster one (whole block, us, these tiles against
+// it): D = 256, F = 256, 2048 / 8192 / 16384 tokens 74 / 97 / 121 against 52 /
+// 87 / 132; D = 1024, F = 256, 2048 / 4096 / 8192 tokens 120 / 136 / 210
+// against 99 / 138 / 234.
 constexpr int kTileQkv = 30;     // TILE_PP_256
 constexpr int kTileNarrow = 13;  // TILE_BD_64x256
-constexpr int kTileGateUp = 4;   // TILE_128x256
+constexpr int kTileGateUp = 31;  // TILE_PP_128
 
 // C[T][ldc] (+)= A[T][K] W^T over one group of all T rows, W a blocked bf16
 // [N][K] matrix.
@@ -868,10 +844,19 @@ readme_status readme_router_tf(int64_t T, int32_t R, int64_t D, int64_t F, int32
     const char* pk = reinterpret_cast<const char*>(packed);
     const int H = (int)(D / kHeadDim);
 
-    // Tiles of the four GEMMs (K = D): measured on MI355X at Table 1's widths
-    // over 8192 tokens, where the automatic choice (tuned for the experts'
-    // K of 4096 - 8192) leaves most CUs idle on the N = D products.
-    const bool wide = T >= 2048 && D <= 1024;
+    const bool wide = T * D >= (int64_t)4 << 20 && D <= 1024;
+    const void* mlp = pk + 4 * D * D * 2;
+    if (D == kFusedRouterWidth && padded_I(F) <= kFusedRouterMlp && T >= fused_router_tokens(F) &&
+        get_gemm_tile() == 0) {
+        hipError_t e = launch_router_head(T, R, V, rms_eps, tokens, req_offsets, emb, x, a, pos,
+                                          offs, pk, qkv, s);
+        if (e == hipSuccess)
+            e = launch_attention(T, H, R, pos, qkv, qkv + D, qkv + 2 * D, 3 * D, o, D, s);
+        if (e == hipSuccess)
+            e = launch_router_tail(T, F, E, rms_eps, o, pk + 3 * D * D * 2, mlp, w_router, bias, x,
+                                   m, h, feat, expert_ids, logits, s);
+        return st_of(e);
+    }
     hipError_t e = launch_embed_norm(T, D, R, V, rms_eps, tokens, req_offsets, emb, x, a, pos,
                                      offs, s);
     if (e == hipSuccess) {
@@ -888,7 +873,6 @@ readme_status readme_router_tf(int64_t T, int32_t R, int64_t D, int64_t F, int32
         e = launch_grouped_gemm(false, EPI_RESID_ADD, g, s);
     }
     if (e == hipSuccess) e = launch_rms_rows(T, D, rms_eps, x, m, s);
-    const void* mlp = pk + 4 * D * D * 2;
     if (e == hipSuccess) {
         GemmArgs gu = gate_up_args(README_BF16, T, D, 1, F, m, offs, mlp, h);
         gu.m_tiles32 = (int)ceil_div(T, 32);

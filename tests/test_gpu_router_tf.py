@@ -325,3 +325,18 @@ def test_router_tf_empty_batch():
     ids, _, _ = L.readme_router_tf(tokens, ro, to_dev(w["emb"]), packed, shape.F,
                                    to_dev(w["w_router"]))
     assert ids.numel() == 0
+
+
+@pytest.mark.parametrize("lengths,F,E", [
+    ([1890], 64, 1),
+    ([0, 1000, 1, 0, 1159], 200, 20),
+    ([33] * 120 + [5], 1500, 8),
+    ([7, 505] * 5 + [1], 512, 44),
+])
+def test_fused_kernels_every_stage(lengths, F, E):
+    """The two fused kernels (D = 512, from 1800 + 1.4 F tokens) at token counts
+    off their 32-token tiles, MLP widths from one K-step to the widest they
+    take, ids outside the vocabulary and empty requests."""
+    shape = wl.RouterShape(D=512, F=F, V=1000, E=E)
+    w, tokens, ro, ids, logits, g = _forward(shape, lengths, 31, bad_tokens=True)
+    _stage_checks(w, tokens, ro, ids, logits, g)
