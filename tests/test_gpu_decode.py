@@ -30,7 +30,7 @@ def _ids(T, E, spread, seed=5):
     return np.random.default_rng(seed).integers(0, E, T).astype(np.int32)
 
 
-# K-steps of 64 in the two GEMMs: fewer than the eight ranges (1, 2, 3), not a
+# K-steps of 64 in the two GEMMs: fewer than the four ranges (1, 2, 3), not a
 # multiple of them (9, 17, 22), and enough that every kernel's loop turns.
 @pytest.mark.parametrize("d,I", [(64, 64), (128, 150), (576, 1040), (1088, 1376), (4096, 96)])
 @pytest.mark.parametrize("T,E,spread", [(1, 8, "one"), (2, 2, "any"), (5, 3, "any"),
@@ -59,7 +59,7 @@ def test_layer_rows(L, oracle_mod, d, I, T, E, spread):
 @pytest.mark.parametrize("spread", ["one", "any"])
 def test_stack_counts_and_offload_agree(L, oracle_mod, T, d, I, spread):
     """Counts known or not, weights resident or cached, the norm inside the
-    gate/up (up to two rows) or before it: the same bits, and the oracle's."""
+    gate/up (one row) or before it: the same bits, and the oracle's."""
     E, layers = 8, 2
     w = wl.Workload("t", T=T, d=d, E=E, I=I, dtype="bf16", layers=layers)
     host = [wl.make_experts(w, 11, layer=k) for k in range(layers)]
