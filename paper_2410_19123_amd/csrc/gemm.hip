@@ -83,6 +83,19 @@ static float decode_cost(int cols, const GemmArgs& g, float m) {
     return rounds * ((cols == 128 ? 1.5f : 2.5f) + bytes / 46000.0f);
 }
 
+// fp32 launches of up to 4096 32 x 64 tiles (half a tile of padding per row
+// group), where each wave's chain of 32x32x2 MFMAs (64 clocks each) and the
+// idle SIMDs weigh most: 32 x 32 outputs per wave.  Whole layers, us, the
+// taller tiles below against this one: 256 tokens, d 512, 4 experts of 512
+// 58.2 -> 40.9; 512 tokens on one 165 -> 40.7; 600 tokens on 64 experts of 256
+// 85.3 -> 73.5; 2048 tokens, d 2048, 4 experts of 1500 (3168 tiles) 1096 ->
+// 758; no size up to that was slower.
+static bool f32_small(const GemmArgs& g) {
+    const int64_t groups = g.E + g.shared_groups;
+    const int64_t rows = g.T * (1 + g.shared_groups);
+    return (rows / 32 + groups / 2) * ceil_div(g.N, 64) <= 4096;
+}
+
 // Tile of a launch.  bf16, by the estimates above.  Decode (the 32 x 128 tile
 // would be the cheapest of the fixed heights, whatever the split over
 // experts): the kernels of one summation order (gemm_decode.hpp), among which
@@ -94,6 +107,7 @@ static int tile_by_shape(bool f32, bool gate_up, const GemmArgs& g) {
     if (f > 0) return f;
     if (g.tile > TILE_AUTO && g.tile <= TILE_LAST) return g.tile;
     if (f32) {  // both operands through LDS (the other kernels are bf16 only)
+        if (f32_small(g)) return TILE_F32_32x64_W2;
         const int64_t per_expert = g.T / (g.E > 0 ? g.E : 1);
         if (per_expert >= (gate_up ? 768 : 192)) return TILE_256x256;
         return per_expert >= 96 && !gate_up ? TILE_128x256 : TILE_32x128;

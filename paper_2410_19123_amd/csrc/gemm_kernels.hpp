@@ -413,12 +413,13 @@ struct Epilogue {
 // wave per 32-row weight group): the gate columns of neuron group n are in
 // wave 2n, the up columns in wave 2n+1, so the pair meets in LDS.  The
 // waves put their fp32 sums into a row-major LDS tile, then all threads form
-// h = silu(g) * u for 8 neurons at a time and store whole output rows with
-// 16-byte stores (same fp32 arithmetic as Epilogue, so the same bits).  A
-// tall tile of many waves goes through LDS CH 32-row blocks at a time.
-template <int TM, int NW>
+// h = silu(g) * u for 16 bytes of neurons at a time and store whole output
+// rows with 16-byte stores (same fp32 arithmetic as Epilogue, so the same
+// bits).  A tall tile of many waves goes through LDS CH 32-row blocks at a time.
+template <int TM, int NW, bool F32 = false>
 struct EpiloguePairWaves {
-    using OT = uint16_t;
+    using OT = std::conditional_t<F32, float, uint16_t>;
+    static constexpr int PC = 16 / (int)sizeof(OT);          // neurons per 16-byte piece
     static constexpr int LDF = NW * 32 + 4;                  // fp32 row pitch
     // 32-row blocks staged at once: the most (dividing TM) that fit 72 KB.
     static constexpr int chunk() {
@@ -428,7 +429,7 @@ struct EpiloguePairWaves {
     }
     static constexpr int CH = chunk();
     static constexpr int LDS_BYTES = CH * 32 * LDF * 4;
-    static constexpr int PER_ROW = NW * 2;                   // 8-neuron pieces per row
+    static constexpr int PER_ROW = NW * 16 / PC;             // pieces per row
     static_assert(NW % 2 == 0, "gate and up waves come in pairs");
 
     __device__ static void run(const GemmArgs& g, const f32x16 (&acc)[TM][1], int wm, int wn,
@@ -453,23 +454,26 @@ struct EpiloguePairWaves {
                 const int rl = u / PER_ROW, pc = u - rl * PER_ROW;  // row in the block
                 const int rt = c0 * 32 + rl;                        // row in the tile
                 if (rt >= rows) continue;
-                const int64_t col = oc0 + (int64_t)pc * 8;
+                const int64_t col = oc0 + (int64_t)pc * PC;
                 if (col >= n_out) continue;
                 const int64_t grow = g.c_rows ? (int64_t)crow[rt] : m0 + rt;
                 if (grow < 0 || grow >= g.T) continue;
-                const int ng = pc / 4, w0 = (pc % 4) * 8;  // neuron group, first neuron in it
+                const int ng = pc / (32 / PC), w0 = (pc % (32 / PC)) * PC;  // neuron group, first neuron in it
                 const float* gt = L + rl * LDF + (2 * ng) * 32 + w0;
                 const float* up = L + rl * LDF + (2 * ng + 1) * 32 + w0;
                 uint32_t packed[4];
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
+                    if constexpr (F32) {
+                        packed[k] = __float_as_uint(silu_f32(gt[k]) * up[k]);
+                        continue;
+                    }
                     const uint32_t lo = f32_to_bf16(silu_f32(gt[2 * k]) * up[2 * k]);
                     const uint32_t hi = f32_to_bf16(silu_f32(gt[2 * k + 1]) * up[2 * k + 1]);
                     packed[k] = lo | (hi << 16);
                 }
                 const u32x4 v = {packed[0], packed[1], packed[2], packed[3]};
-                *reinterpret_cast<u32x4*>(reinterpret_cast<uint16_t*>(g.C) + grow * g.ldc + col) =
-                    v;
+                *reinterpret_cast<u32x4*>(reinterpret_cast<OT*>(g.C) + grow * g.ldc + col) = v;
             }
         }
     }
@@ -494,10 +498,14 @@ __global__ __launch_bounds__(WGM* WGN * 64) void k_grouped_gemm(GemmArgs args) {
     constexpr int STAGE = (BM + BN) * KC;  // u32x4 slots per stage
     static_assert(WM % 32 == 0 && WN % 32 == 0, "wave tile");
     static_assert(A_INS * RPI * NW == BM && B_INS * RPI * NW == BN, "DMA split");
-    static_assert(EPI != EPI_GATE_UP_SILU || WN % 64 == 0, "gate/up pairs");
+    // Waves of one 32-column group: gate and up meet across two of them.
+    constexpr bool PAIR = EPI == EPI_GATE_UP_SILU && TN == 1;
+    static_assert(EPI != EPI_GATE_UP_SILU || (PAIR ? WGM == 1 : WN % 64 == 0), "gate/up pairs");
     static_assert(NSTAGE >= 2 && LPS * (NSTAGE - 2) < 64, "stages");
 
-    using Epi = Epilogue<TM, TN, WGM, WGN, F32, EPI, (NSTAGE * STAGE * 16 > 73728 ? NSTAGE * STAGE * 16 : 73728)>;
+    constexpr int BUDGET = NSTAGE * STAGE * 16 > 73728 ? NSTAGE * STAGE * 16 : 73728;
+    using Epi = std::conditional_t<PAIR, EpiloguePairWaves<TM, PAIR ? WGN : 2, F32>,
+                                   Epilogue<TM, TN, WGM, WGN, F32, EPI, BUDGET>>;
     constexpr int LDS_SLOTS = NSTAGE * STAGE > Epi::LDS_BYTES / 16 ? NSTAGE * STAGE : Epi::LDS_BYTES / 16;
     __shared__ u32x4 lds[LDS_SLOTS];
     __shared__ int32_t crow[BM];  // output row of each tile row (row map)
@@ -953,6 +961,9 @@ enum TileCfg {
     TILE_SKINNY_32 = 33,  // 32 rows x 32 columns
     TILE_SKINNY_64 = 34,  // 32 rows x 64 columns
     TILE_DECODE_128 = 35,  // 32 rows x 128 columns
+    // fp32 launches that leave the chip idle: 32 x 64, 2 waves of 32x32, 6
+    // stages, 72 KB (2 per CU).
+    TILE_F32_32x64_W2 = 36,
 };
 
 // Launches one tile configuration (instantiated per element type and
@@ -973,6 +984,9 @@ hipError_t launch_tile(int tile, GemmArgs g, hipStream_t s) {
         case TILE_256x256_K32: return launch_cfg<256, 256, 2, 4, 4, F32, EPI, 4>(g, s);
         case TILE_128x256_K32: return launch_cfg<128, 256, 2, 4, 6, F32, EPI, 4>(g, s);
         default: break;
+    }
+    if constexpr (F32) {
+        if (tile == TILE_F32_32x64_W2) return launch_cfg<32, 64, 1, 2, 6, F32, EPI>(g, s);
     }
     if constexpr (!F32) {
         switch (tile) {
