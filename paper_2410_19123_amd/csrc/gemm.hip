@@ -83,17 +83,26 @@ static float decode_cost(int cols, const GemmArgs& g, float m) {
     return rounds * ((cols == 128 ? 1.5f : 2.5f) + bytes / 46000.0f);
 }
 
-// fp32 launches of up to 4096 32 x 64 tiles (half a tile of padding per row
-// group), where each wave's chain of 32x32x2 MFMAs (64 clocks each) and the
-// idle SIMDs weigh most: 32 x 32 outputs per wave.  Whole layers, us, the
-// taller tiles below against this one: 256 tokens, d 512, 4 experts of 512
-// 58.2 -> 40.9; 512 tokens on one 165 -> 40.7; 600 tokens on 64 experts of 256
-// 85.3 -> 73.5; 2048 tokens, d 2048, 4 experts of 1500 (3168 tiles) 1096 ->
-// 758; no size up to that was slower.
-static bool f32_small(const GemmArgs& g) {
+// fp32: waves of 32 x 32 outputs.  A wave's chain of 32x32x2 MFMAs (64 clocks
+// each) is then half a 32 x 64 wave's, and with two to four small workgroups
+// per CU one wave's LDS waits are covered by another's MFMAs, which the tall
+// tiles (one workgroup per CU, two waves per SIMD) do not reach at any size.
+// Past 64 tokens per expert 64 x 64 tiles; below, 32 x 64 with six K-steps in
+// flight while all tiles (half a tile of padding per row group) are on the
+// chip at once, with three, and so four per CU, past that.  Whole layers, us:
+// tall tiles and 32 x 128 / 32 x 64 six / 32 x 64 three / 64 x 64:
+//   256 tokens, d 512, 4 experts of 512        57 /   40 /   41 /   43
+//   600 tokens, d 512, 64 experts of 256       79 /   68 /   73 /   78
+//   1500 tokens, d 1024, 64 experts of 512    304 /  231 /  199 /  231
+//   300 tokens, d 2048, 4 experts of 1536     261 /  177 /  155 /  145
+//   2048 tokens, d 2048, 4 experts of 1500   1026 /  668 /  489 /  431
+//   8192 tokens, d 4096, 4 experts of 1376   3153 / 4441 / 2988 / 2618
+static int f32_tile(const GemmArgs& g) {
+    if (g.T / (g.E > 0 ? g.E : 1) > 64) return TILE_F32_64x64_W4;
     const int64_t groups = g.E + g.shared_groups;
     const int64_t rows = g.T * (1 + g.shared_groups);
-    return (rows / 32 + groups / 2) * ceil_div(g.N, 64) <= 4096;
+    const int64_t tiles = (rows / 32 + groups / 2) * ceil_div(g.N, 64);
+    return tiles <= 512 ? TILE_F32_32x64_W2 : TILE_F32_32x64_W2_S3;
 }
 
 // Tile of a launch.  bf16, by the estimates above.  Decode (the 32 x 128 tile
@@ -102,16 +111,11 @@ static bool f32_small(const GemmArgs& g) {
 // the caller's counts may choose.  Else 64 x 256 (four waves) or one of the
 // mixed-height launches of gemm_pp.hpp, whose tall tiles are the fastest per
 // flop.
-static int tile_by_shape(bool f32, bool gate_up, const GemmArgs& g) {
+static int tile_by_shape(bool f32, const GemmArgs& g) {
     const int f = forced_tile();
     if (f > 0) return f;
     if (g.tile > TILE_AUTO && g.tile <= TILE_LAST) return g.tile;
-    if (f32) {  // both operands through LDS (the other kernels are bf16 only)
-        if (f32_small(g)) return TILE_F32_32x64_W2;
-        const int64_t per_expert = g.T / (g.E > 0 ? g.E : 1);
-        if (per_expert >= (gate_up ? 768 : 192)) return TILE_256x256;
-        return per_expert >= 96 && !gate_up ? TILE_128x256 : TILE_32x128;
-    }
+    if (f32) return f32_tile(g);  // both operands through LDS (the other kernels are bf16 only)
     const float c64 = tile_cost(64, g), c128 = tile_cost(128, g), c256 = tile_cost(256, g);
     if (decode_launch(g)) {
         const float m = decode_m_tiles(g);
@@ -143,7 +147,7 @@ hipError_t launch_grouped_gemm(bool f32, int epi, GemmArgs g, hipStream_t s) {
     if (g.b_expert_stride * (f32 ? 4 : 2) > INT32_MAX) return hipErrorInvalidValue;
     if (g.K >= (int64_t)32 << 16) return hipErrorInvalidValue;
     if (g.k_segs > 1 && epi != EPI_STORE) return hipErrorInvalidValue;  // segments: down only
-    int tile = tile_by_shape(f32, epi == EPI_GATE_UP_SILU, g);
+    int tile = tile_by_shape(f32, g);
     if (g.rms_in) {  // gate_up_takes_norm: a weight stream, of at most 32 columns
         if (tile != TILE_SKINNY_16) tile = TILE_SKINNY_32;
         return launch_decode_bf16(tile, epi, g, s);

@@ -416,8 +416,9 @@ struct Epilogue {
 // h = silu(g) * u for 16 bytes of neurons at a time and store whole output
 // rows with 16-byte stores (same fp32 arithmetic as Epilogue, so the same
 // bits).  A tall tile of many waves goes through LDS CH 32-row blocks at a time.
-template <int TM, int NW, bool F32 = false>
+template <int TM, int NW, bool F32 = false, int WGM = 1>
 struct EpiloguePairWaves {
+    static_assert(WGM == 1 || TM == 1, "one block per wave row");
     using OT = std::conditional_t<F32, float, uint16_t>;
     static constexpr int PC = 16 / (int)sizeof(OT);          // neurons per 16-byte piece
     static constexpr int LDF = NW * 32 + 4;                  // fp32 row pitch
@@ -428,14 +429,13 @@ struct EpiloguePairWaves {
         return c;
     }
     static constexpr int CH = chunk();
-    static constexpr int LDS_BYTES = CH * 32 * LDF * 4;
+    static constexpr int LDS_BYTES = WGM * CH * 32 * LDF * 4;
     static constexpr int PER_ROW = NW * 16 / PC;             // pieces per row
     static_assert(NW % 2 == 0, "gate and up waves come in pairs");
 
     __device__ static void run(const GemmArgs& g, const f32x16 (&acc)[TM][1], int wm, int wn,
                                int64_t n0, int rows, int64_t m0, const int32_t* crow,
                                void* lds_raw, int tid, int nthreads) {
-        (void)wm;
         float* L = reinterpret_cast<float*>(lds_raw);
         const int lane = tid & 63;
         const int64_t oc0 = n0 / 2, n_out = g.N / 2;
@@ -446,11 +446,11 @@ struct EpiloguePairWaves {
             for (int i = 0; i < CH; ++i)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
-                    const int lr = i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+                    const int lr = (wm + i) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
                     L[lr * LDF + wn * 32 + (lane & 31)] = acc[c0 + i][0][r];
                 }
             __syncthreads();
-            for (int u = tid; u < CH * 32 * PER_ROW; u += nthreads) {
+            for (int u = tid; u < WGM * CH * 32 * PER_ROW; u += nthreads) {
                 const int rl = u / PER_ROW, pc = u - rl * PER_ROW;  // row in the block
                 const int rt = c0 * 32 + rl;                        // row in the tile
                 if (rt >= rows) continue;
@@ -500,11 +500,11 @@ __global__ __launch_bounds__(WGM* WGN * 64) void k_grouped_gemm(GemmArgs args) {
     static_assert(A_INS * RPI * NW == BM && B_INS * RPI * NW == BN, "DMA split");
     // Waves of one 32-column group: gate and up meet across two of them.
     constexpr bool PAIR = EPI == EPI_GATE_UP_SILU && TN == 1;
-    static_assert(EPI != EPI_GATE_UP_SILU || (PAIR ? WGM == 1 : WN % 64 == 0), "gate/up pairs");
+    static_assert(EPI != EPI_GATE_UP_SILU || (PAIR || WN % 64 == 0), "gate/up pairs");
     static_assert(NSTAGE >= 2 && LPS * (NSTAGE - 2) < 64, "stages");
 
     constexpr int BUDGET = NSTAGE * STAGE * 16 > 73728 ? NSTAGE * STAGE * 16 : 73728;
-    using Epi = std::conditional_t<PAIR, EpiloguePairWaves<TM, PAIR ? WGN : 2, F32>,
+    using Epi = std::conditional_t<PAIR, EpiloguePairWaves<PAIR ? TM : 1, PAIR ? WGN : 2, F32, WGM>,
                                    Epilogue<TM, TN, WGM, WGN, F32, EPI, BUDGET>>;
     constexpr int LDS_SLOTS = NSTAGE * STAGE > Epi::LDS_BYTES / 16 ? NSTAGE * STAGE : Epi::LDS_BYTES / 16;
     __shared__ u32x4 lds[LDS_SLOTS];
@@ -961,9 +961,10 @@ enum TileCfg {
     TILE_SKINNY_32 = 33,  // 32 rows x 32 columns
     TILE_SKINNY_64 = 34,  // 32 rows x 64 columns
     TILE_DECODE_128 = 35,  // 32 rows x 128 columns
-    // fp32 launches that leave the chip idle: 32 x 64, 2 waves of 32x32, 6
-    // stages, 72 KB (2 per CU).
-    TILE_F32_32x64_W2 = 36,
+    // fp32, waves of 32 x 32:
+    TILE_F32_32x64_W2 = 36,     // 1x2 waves, 6 stages, 72 KB (2 per CU)
+    TILE_F32_32x64_W2_S3 = 37,  // 1x2 waves, 3 stages, 36 KB (4 per CU)
+    TILE_F32_64x64_W4 = 38,     // 2x2 waves, 3 stages, 48 KB (3 per CU)
 };
 
 // Launches one tile configuration (instantiated per element type and
@@ -987,6 +988,8 @@ hipError_t launch_tile(int tile, GemmArgs g, hipStream_t s) {
     }
     if constexpr (F32) {
         if (tile == TILE_F32_32x64_W2) return launch_cfg<32, 64, 1, 2, 6, F32, EPI>(g, s);
+        if (tile == TILE_F32_32x64_W2_S3) return launch_cfg<32, 64, 1, 2, 3, F32, EPI>(g, s);
+        if (tile == TILE_F32_64x64_W4) return launch_cfg<64, 64, 2, 2, 3, F32, EPI>(g, s);
     }
     if constexpr (!F32) {
         switch (tile) {

@@ -1,5 +1,5 @@
-"""The fp32 tile of small launches (32 x 64, two waves of 32 x 32 whose gate
-and up sums meet in LDS) where its rows, columns and K-steps can go wrong:
+"""The fp32 tiles of 32 x 32 waves (32 x 64 and 64 x 64; gate and up sums meet
+in LDS) where its rows, columns and K-steps can go wrong:
 against the oracle, and the same bits as the 32 x 128 tile, which adds K in
 the same order."""
 import numpy as np
@@ -26,7 +26,8 @@ def oracle_mod():
 
 # K-steps (of 32) below, at and past the six in flight; one column tile to many.
 @pytest.mark.parametrize("d,I", [(64, 40), (128, 64), (192, 250), (576, 330)])
-@pytest.mark.parametrize("counts", [[1], [0, 31, 0], [32, 33, 1], [129, 0, 64, 95]])
+@pytest.mark.parametrize("counts", [[1], [0, 31, 0], [32, 33, 1], [129, 0, 64, 95],
+                                    [65], [1] * 60 + [33] * 10])
 def test_rows_columns_and_k_steps(L, oracle_mod, d, I, counts):
     E, T = len(counts), sum(counts)
     w = wl.Workload("t", T=T, d=d, E=E, I=I, dtype="f32")
