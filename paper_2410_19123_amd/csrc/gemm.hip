@@ -135,6 +135,17 @@ static int tile_by_shape(bool f32, const GemmArgs& g) {
     return c128 <= c256 ? TILE_PP_128 : TILE_PP_256;
 }
 
+// The tile a launch runs: tile_by_shape, or the tile that takes its place where
+// activation offsets do not fit the 32 bits (of 16 bytes each) that
+// gemm_pp.hpp and the weight streams of gemm_decode.hpp keep them in.  The
+// fp32 tiles address in 64 bits.
+static int launch_tile_number(bool f32, const GemmArgs& g) {
+    const int tile = tile_by_shape(f32, g);
+    if (f32 || g.T * (g.lda >> 3) <= INT32_MAX) return tile;
+    if (is_pp_tile(tile)) return TILE_MIX_256;
+    return tile >= TILE_SKINNY_16 ? TILE_DECODE_128 : tile;
+}
+
 bool gate_up_takes_norm(GemmArgs g) {
     if (forced_tile() > 0 || g.T > kNormRows || g.K > kNormWidth) return false;
     return decode_launch(g);
@@ -147,15 +158,11 @@ hipError_t launch_grouped_gemm(bool f32, int epi, GemmArgs g, hipStream_t s) {
     if (g.b_expert_stride * (f32 ? 4 : 2) > INT32_MAX) return hipErrorInvalidValue;
     if (g.K >= (int64_t)32 << 16) return hipErrorInvalidValue;
     if (g.k_segs > 1 && epi != EPI_STORE) return hipErrorInvalidValue;  // segments: down only
-    int tile = tile_by_shape(f32, g);
+    int tile = launch_tile_number(f32, g);
     if (g.rms_in) {  // gate_up_takes_norm: a weight stream, of at most 32 columns
         if (tile != TILE_SKINNY_16) tile = TILE_SKINNY_32;
         return launch_decode_bf16(tile, epi, g, s);
     }
-    // gemm_pp.hpp and gemm_decode.hpp keep activation offsets in 32 bits of 16
-    // bytes each.
-    if (is_pp_tile(tile) && g.T * (g.lda >> 3) > INT32_MAX) tile = TILE_MIX_256;
-    if (tile >= TILE_SKINNY_16 && g.T * (g.lda >> 3) > INT32_MAX) tile = TILE_DECODE_128;
     if (!f32 && tile >= TILE_SKINNY_16) return launch_decode_bf16(tile, epi, g, s);
     if (!f32 && is_pp_tile(tile)) {
         if (epi == EPI_GATE_UP_SILU) return launch_pp_bf16_gate_up(tile, g, s);
@@ -177,3 +184,18 @@ hipError_t launch_grouped_gemm(bool f32, int epi, GemmArgs g, hipStream_t s) {
 }
 
 }  // namespace readme
+
+// Outside readme.h, for tests: the tile number (TileCfg) of a GEMM launch with
+// these sizes and the calling thread's override.
+extern "C" int32_t readme_internal_gemm_tile(int32_t f32, int64_t T, int64_t N, int64_t K,
+                                             int32_t E, int32_t shared_groups,
+                                             int32_t m_tiles32) {
+    readme::GemmArgs g{};
+    g.T = T;
+    g.N = N;
+    g.K = g.lda = K;
+    g.E = E;
+    g.shared_groups = shared_groups;
+    g.m_tiles32 = m_tiles32;
+    return readme::launch_tile_number(f32 != 0, g);
+}

@@ -1,0 +1,39 @@
+"""The tile a grouped GEMM launch takes, by its sizes alone (no GPU: the rule is
+host code)."""
+import ctypes
+import os
+
+import pytest
+
+# Tile numbers of the kernels no override reaches.
+SKINNY_16, SKINNY_32, SKINNY_64, DECODE_128 = 32, 33, 34, 35
+F32_32x64, F32_32x64_S3, F32_64x64 = 36, 37, 38
+INT32_MAX = 2 ** 31 - 1
+
+
+@pytest.fixture(scope="module")
+def tile():
+    from paper_2410_19123_amd import _lib
+    if not os.path.exists(_lib.LIB_PATH):
+        pytest.skip("libreadme.so not built")
+    fn = _lib.load().readme_internal_gemm_tile
+    fn.restype = ctypes.c_int32
+    fn.argtypes = [ctypes.c_int32] + [ctypes.c_int64] * 3 + [ctypes.c_int32] * 3
+    return lambda T, N, K, E, f32=False, shared=0, m32=0: fn(f32, T, N, K, E, shared, m32)
+
+
+@pytest.mark.parametrize("T,N,K,E,want", [
+    (4 << 20, 1024, 8192, 8, F32_64x64),
+    (1 << 28, 64, 128, 1, F32_64x64),
+    (256, 1024, 512, 4, F32_32x64),
+])
+def test_fp32_keeps_its_tiles_past_32_bit_offsets(tile, T, N, K, E, want):
+    assert tile(T, N, K, E, f32=True) == want
+
+
+def test_bf16_past_32_bit_offsets(tile):
+    """Tiles whose activation offsets are 32-bit give way to 64-bit ones."""
+    T = 4 << 20
+    assert T * 8192 // 8 > INT32_MAX
+    assert tile(T // 8, 1024, 8192, 8) == 30
+    assert tile(T, 1024, 8192, 8) == 24
