@@ -97,8 +97,13 @@ static float decode_cost(int cols, const GemmArgs& g, float m) {
 //   300 tokens, d 2048, 4 experts of 1536     261 /  177 /  155 /  145
 //   2048 tokens, d 2048, 4 experts of 1500   1026 /  668 /  489 /  431
 //   8192 tokens, d 4096, 4 experts of 1376   3153 / 4441 / 2988 / 2618
+// A grid holds fewer than 2^32 threads: past 2^24 tiles of 64 x 64 (256 threads,
+// so 2^36 outputs) the launch takes 256 x 256 tiles, a sixteenth as many.
 static int f32_tile(const GemmArgs& g) {
-    if (g.T / (g.E > 0 ? g.E : 1) > 64) return TILE_F32_64x64_W4;
+    if (g.T / (g.E > 0 ? g.E : 1) > 64) {
+        const int64_t tiles = m_tiles_bound(g, 64) * ceil_div(g.N, 64);
+        return tiles < (1 << 24) - 8 ? TILE_F32_64x64_W4 : TILE_256x256;
+    }
     const int64_t groups = g.E + g.shared_groups;
     const int64_t rows = g.T * (1 + g.shared_groups);
     const int64_t tiles = (rows / 32 + groups / 2) * ceil_div(g.N, 64);

@@ -37,3 +37,14 @@ def test_bf16_past_32_bit_offsets(tile):
     assert T * 8192 // 8 > INT32_MAX
     assert tile(T // 8, 1024, 8192, 8) == 30
     assert tile(T, 1024, 8192, 8) == 24
+
+
+@pytest.mark.parametrize("T,N,E,shared", [(1 << 21, 1 << 15, 4, 0), ((1 << 21) - 512, 1 << 15, 1, 0),
+                                          (1 << 20, 1 << 15, 4, 1), (1 << 26, 1 << 12, 256, 0)])
+def test_fp32_grids_stay_below_2_to_32_threads(tile, T, N, E, shared):
+    """Tiles (rounded up to 8) times threads of the chosen tile: a grid's size
+    in threads is a 32-bit number."""
+    rows_cols_threads = {F32_64x64: (64, 64, 256), 1: (256, 256, 512)}
+    h, w, threads = rows_cols_threads[tile(T, N, 64, E, f32=True, shared=shared)]
+    m = (T + E * (h - 1)) // h + shared * -(-T // h)
+    assert -(-m * -(-N // w) // 8) * 8 * threads < 2 ** 32
