@@ -21,38 +21,56 @@ bool set_gemm_tile(int tile) {
 
 int get_gemm_tile() { return t_forced_tile; }
 
+// Row groups of the launch (experts, then permanent groups) and their rows.
+static int64_t row_groups(const GemmArgs& g) { return g.E + g.shared_groups; }
+static int64_t group_rows(const GemmArgs& g) { return g.T * (1 + (int64_t)g.shared_groups); }
+
+// Experts that T tokens of a uniform load reach.
+static float active_experts(const GemmArgs& g) {
+    const float E = (float)g.E;
+    return E * (1.0f - powf(1.0f - 1.0f / E, (float)g.T));
+}
+
+// Estimated row tiles of `height` rows: the host does not know the split over
+// experts, so each row group is taken to end in half a tile of padding, and
+// each that has rows at all has a tile.
+static float row_tiles(int height, const GemmArgs& g) {
+    const float groups = active_experts(g) + (float)g.shared_groups;
+    const float full = (float)group_rows(g) / height + 0.5f * groups;
+    return full > groups ? full : groups;
+}
+
 // Estimated time (us, up to a common offset) of one launch on tiles of
-// `height` rows, from the token count, the expert count and the GEMM's size:
-// the host does not know the split over experts, so each row group is taken
-// to end in half a tile of padding.  A tile costs a fixed start and end plus
-// a time per 64-element K-step; up to 256 tiles run at once (one per CU), and
-// past that a round costs more than its share because rounds end ragged.  The
-// constants fit a sweep of all tiles on MI355X (E = 8, 16, 32; d = 1024 ..
-// 8192; 8 .. 768 tokens per expert, uniform and Zipf loads; us of gate/up):
-//   d 4096, I 1376, 64 / 128 / 256 / 768 per expert:
-//     32x128 53/78/120/276, 64x256 57/56/90/185, 128 rows 61/66/66/166,
-//     256 rows 61/75/82/167
-//   d 8192, I 3584, 32 / 64 / 128 / 384 / 768 per expert:
-//     32x128 178/243/340/901/1690, 64x256 152/212/285/496/930,
-//     128 rows 153/156/253/470/739, 256 rows 152/157/186/373/570
+// `height` rows x 256 columns.  A tile costs a fixed start and end plus a time
+// per 64-element K-step; up to 256 tiles run at once (one per CU), and past
+// that a round costs more than its share because rounds end ragged.  The
+// constants fit a sweep of all tiles on MI355X over 2627 layers (d 512 .. 8192,
+// I 256 .. 3584, 1 .. 128 experts, 1 .. 1024 tokens per expert; uniform, Zipf
+// and one-expert loads; 1.3% of the 5254 GEMMs run more than 4% longer than
+// on the tiles that were chosen by tokens per expert alone, 8.6% without the
+// tile per row group and with other constants); us of gate/up, uniform load,
+// 32x128 / 64x256 / 128 rows / 256 rows:
+//   d 6400, I 955, 32 experts of 48 tokens      163 / 198 / 195 / 196
+//   d 1024, I 512, 128 experts of 64             73 /  59 /  76 /  78
+//   d 4096, I 1376, 8 experts of 128             78 /  56 /  66 /  75
+//   d 8192, I 3584, 4 experts of 192            236 / 179 / 128 / 151
 static float tile_cost(int height, const GemmArgs& g) {
     const float nk = (float)g.K / 64.0f;
-    const int64_t groups = g.E + g.shared_groups;
-    const int64_t rows = g.T * (1 + g.shared_groups);
-    const float tiles = ((float)rows / height + 0.5f * groups) * ceil_div(g.N, 256) / 256.0f;
-    const float rounds = tiles <= 1.0f ? 1.0f : tiles + 0.4f;
-    if (height == 64) return rounds * (5.0f + 0.75f * nk);
-    if (height == 128) return rounds * (5.6f + 0.92f * nk);
-    return rounds * (6.4f + 1.22f * nk);
+    const float tiles = row_tiles(height, g) * ceil_div(g.N, 256) / 256.0f;
+    const float rounds = tiles <= 1.0f ? 1.0f : tiles + 0.25f;
+    if (height == 64) return rounds * (5.0f + 0.78f * nk);
+    if (height == 128) return rounds * (6.5f + 0.95f * nk);
+    return rounds * (10.0f + 0.97f * nk);
 }
 
 // Whether the launch is a decode launch: by its sizes alone, never by the
-// counts, since the summation order follows from it.
+// counts, since the summation order follows from it.  Under 28 rows per group
+// always: a taller tile is then more padding than rows, and the weights it
+// streams come in with fewer workgroups (64 x 256 against 32 x 128, 16 to 64
+// experts: 1.02 to 1.10 times as long at 8 rows, 0.89 to 0.97 at 32).
 static bool decode_launch(const GemmArgs& g) {
-    const float tiles =
-        ((float)(g.T * (1 + g.shared_groups)) / 32.0f + 0.5f * (g.E + g.shared_groups)) *
-        ceil_div(g.N, 128) / 256.0f;
-    const float t = 0.42f * tiles;
+    if (group_rows(g) < 28 * row_groups(g)) return true;
+    const float t = 0.42f * row_tiles(32, g) * ceil_div(g.N, 128) / 256.0f;
     const float cost = 3.0f + (float)g.K / 64.0f * (t > 0.5f ? t : 0.5f);
     return cost <= tile_cost(64, g) && cost <= tile_cost(128, g) && cost <= tile_cost(256, g);
 }
@@ -62,10 +80,9 @@ static bool decode_launch(const GemmArgs& g) {
 // of padding for each expert when they fill tiles.
 static float decode_m_tiles(const GemmArgs& g) {
     if (g.m_tiles32 > 0) return (float)g.m_tiles32;
-    const float T = (float)g.T, E = (float)g.E;
-    const float active = E * (1.0f - powf(1.0f - 1.0f / E, T));
-    const float full = T / 32.0f + 0.5f * active;
-    const float m = (active > full ? active : full) + g.shared_groups * ceilf(T / 32.0f);
+    const float active = active_experts(g);
+    const float full = (float)g.T / 32.0f + 0.5f * active;
+    const float m = (active > full ? active : full) + g.shared_groups * ceilf((float)g.T / 32.0f);
     const float bound = (float)m_tiles_bound(g, 32);
     return m < bound ? m : bound;
 }

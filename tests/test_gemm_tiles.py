@@ -48,3 +48,21 @@ def test_fp32_grids_stay_below_2_to_32_threads(tile, T, N, E, shared):
     h, w, threads = rows_cols_threads[tile(T, N, 64, E, f32=True, shared=shared)]
     m = (T + E * (h - 1)) // h + shared * -(-T // h)
     assert -(-m * -(-N // w) // 8) * 8 * threads < 2 ** 32
+
+
+@pytest.mark.parametrize("d,I", [(512, 256), (1024, 2816), (4096, 1376), (8192, 3584)])
+@pytest.mark.parametrize("E", [8, 16, 64, 256])
+def test_few_rows_per_expert_take_32_row_tiles(tile, d, I, E):
+    """Up to 27 rows per expert, however many experts: a taller tile would be
+    mostly padding and leave fewer workgroups to stream the weights."""
+    Ip = (I + 63) // 64 * 64
+    for per in (1, 8, 16, 27):
+        for N, K in ((2 * Ip, d), (d, Ip)):
+            assert tile(per * E, N, K, E) in (SKINNY_16, SKINNY_32, SKINNY_64, DECODE_128, 27)
+
+
+def test_a_row_group_is_at_least_one_tile(tile):
+    """Many experts whose rows fill a small part of a tall tile: the estimate
+    counts a tile for each, not the rows' share of one."""
+    for E, N, K in ((64, 1024, 1024), (32, 2816, 4096), (16, 7168, 8192)):
+        assert tile(E * 40, N, K, E) != 30
