@@ -501,6 +501,7 @@ readme_status stack_impl(int64_t T, int64_t d, int32_t E, int64_t I, int32_t L,
         hipError_t err = hipSuccess;
         GemmArgs gu = gate_up_args(README_BF16, T, d, E, I, xn, offsets, packed_per_layer[l], h);
         gu.m_tiles32 = m32;
+        gu.counts_order = true;
         gu.rms_in = gate_up_takes_norm(gu);
         if (gu.rms_in) {
             gu.A = x_resid_grouped;
@@ -514,6 +515,7 @@ readme_status stack_impl(int64_t T, int64_t d, int32_t E, int64_t I, int32_t L,
         GemmArgs dn = down_args(README_BF16, T, d, E, I, h, offsets, packed_per_layer[l],
                                 x_resid_grouped);
         dn.m_tiles32 = m32;
+        dn.counts_order = true;
         err = launch_grouped_gemm(false, EPI_RESID_ADD, dn, s);
         if (err != hipSuccess) return README_ERR_HIP;
     }

@@ -129,8 +129,14 @@ static int f32_tile(const GemmArgs& g) {
 
 // Tile of a launch.  bf16, by the estimates above.  Decode (the 32 x 128 tile
 // would be the cheapest of the fixed heights, whatever the split over
-// experts): the kernels of one summation order (gemm_decode.hpp), among which
-// the caller's counts may choose.  Else 64 x 256 (four waves) or one of the
+// experts): the kernels of gemm_decode.hpp, whose one summation order lets the
+// caller's counts choose among them.  Where no caller can give counts (a layer
+// outside a stack), the 32 x 128 tile is the register-streamed one instead: it
+// keeps six K-steps in flight where the other has registers for five, and was
+// the faster one of 4314 GEMMs by 1 to 2% at the median, by 7 to 16% (1 to 3 us)
+// where fewer than 64 tiles have rows, so that a CU has one workgroup that waits
+// for its own loads, and K is 1024 or more; with K below that it is 3% (0.2 us)
+// slower there.  Else 64 x 256 (four waves) or one of the
 // mixed-height launches of gemm_pp.hpp, whose tall tiles are the fastest per
 // flop.
 static int tile_by_shape(bool f32, const GemmArgs& g) {
@@ -151,6 +157,7 @@ static int tile_by_shape(bool f32, const GemmArgs& g) {
                 best = i;
             }
         }
+        if (best == 0 && !g.counts_order) return TILE_BD_32x128_W4;
         return tile[best];
     }
     if (c64 <= c128 && c64 <= c256) return TILE_BD_64x256;
@@ -211,7 +218,7 @@ hipError_t launch_grouped_gemm(bool f32, int epi, GemmArgs g, hipStream_t s) {
 // these sizes and the calling thread's override.
 extern "C" int32_t readme_internal_gemm_tile(int32_t f32, int64_t T, int64_t N, int64_t K,
                                              int32_t E, int32_t shared_groups,
-                                             int32_t m_tiles32) {
+                                             int32_t m_tiles32, int32_t counts_order) {
     readme::GemmArgs g{};
     g.T = T;
     g.N = N;
@@ -219,5 +226,6 @@ extern "C" int32_t readme_internal_gemm_tile(int32_t f32, int64_t T, int64_t N, 
     g.E = E;
     g.shared_groups = shared_groups;
     g.m_tiles32 = m_tiles32;
+    g.counts_order = counts_order != 0;
     return readme::launch_tile_number(f32 != 0, g);
 }

@@ -47,6 +47,10 @@ struct GemmArgs {
     // m_tiles32 > 0: sum over experts of ceil(rows_e / 32), from token counts
     // the caller knows on the host (the tile choice then sees the split).
     int m_tiles32;
+    // counts_order: the launch's sums must have the order they have in a call
+    // that knows other counts, or none (a stack, whose results do not depend on
+    // them).
+    bool counts_order;
     // tile > 0: this launch's tile configuration (a caller that measured its
     // own shapes); the calling thread's override still takes precedence.
     int tile;

@@ -226,6 +226,7 @@ readme_status readme_offload_stack(readme_offload* ex, int64_t T, const int32_t*
         gu.b_expert_stride = slot_elems;
         gu.b_index = dev_table + (size_t)l * E;
         gu.m_tiles32 = m32;
+        gu.counts_order = true;
         if (err == hipSuccess) err = launch_grouped_gemm(false, EPI_GATE_UP_SILU, gu, s);
         GemmArgs dn = down_args(README_BF16, T, ex->d, E, ex->I, h, offsets, ex->dev_slots,
                                 x_resid_grouped);
@@ -233,6 +234,7 @@ readme_status readme_offload_stack(readme_offload* ex, int64_t T, const int32_t*
         dn.b_expert_stride = slot_elems;
         dn.b_index = dev_table + (size_t)l * E;
         dn.m_tiles32 = m32;
+        dn.counts_order = true;
         if (err == hipSuccess) err = launch_grouped_gemm(false, EPI_RESID_ADD, dn, s);
         if (err != hipSuccess || hipEventRecord(ex->done[l], s) != hipSuccess) return fail();
     }

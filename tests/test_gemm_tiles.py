@@ -18,8 +18,9 @@ def tile():
         pytest.skip("libreadme.so not built")
     fn = _lib.load().readme_internal_gemm_tile
     fn.restype = ctypes.c_int32
-    fn.argtypes = [ctypes.c_int32] + [ctypes.c_int64] * 3 + [ctypes.c_int32] * 3
-    return lambda T, N, K, E, f32=False, shared=0, m32=0: fn(f32, T, N, K, E, shared, m32)
+    fn.argtypes = [ctypes.c_int32] + [ctypes.c_int64] * 3 + [ctypes.c_int32] * 4
+    return lambda T, N, K, E, f32=False, shared=0, m32=0, stack=False: fn(f32, T, N, K, E, shared,
+                                                                          m32, stack)
 
 
 @pytest.mark.parametrize("T,N,K,E,want", [
@@ -66,3 +67,16 @@ def test_a_row_group_is_at_least_one_tile(tile):
     counts a tile for each, not the rows' share of one."""
     for E, N, K in ((64, 1024, 1024), (32, 2816, 4096), (16, 7168, 8192)):
         assert tile(E * 40, N, K, E) != 30
+
+
+@pytest.mark.parametrize("T,E", [(32, 16), (200, 8), (500, 64), (3, 3)])
+def test_32x128_decode_tile_of_layers_and_stacks(tile, T, E):
+    """A stack's tile has one summation order with the weight streams, whatever
+    counts are known; a layer, which knows none, takes the faster tile."""
+    streams = (SKINNY_16, SKINNY_32, SKINNY_64)
+    N, K = 2816, 4096
+    layer, stack = tile(T, N, K, E), tile(T, N, K, E, stack=True)
+    assert stack in streams + (DECODE_128,)
+    assert layer == (27 if stack == DECODE_128 else stack)
+    for m32 in range(1, min(E, T) + 1):
+        assert tile(T, N, K, E, stack=True, m32=m32) in streams + (DECODE_128,)
