@@ -179,8 +179,8 @@ int64_t readme_padded_intermediate(int64_t I);
  *   expert in full tiles of the first height, its remainder in the
  *   shortest that holds it, 256 columns:
  *     24 = 256/128/64/32, 25 = 192/128/64/32, 26 = 128/64/32 (four waves,
- *     weights in registers), 30 = 256/128/64, 31 = 128/64 (eight waves in
- *     two opposite phases, both operands in LDS)
+ *     weights in registers), 30 = 256/128/64 (eight waves in two opposite
+ *     phases, both operands in LDS), 31 = the same as 30
  *   (rows of tokens x columns of outputs)
  * Results do not depend on the tile beyond fp32 summation order.  Returns
  * README_ERR_ARG for any other value.  readme_get_gemm_tile returns the

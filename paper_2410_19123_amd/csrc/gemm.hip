@@ -142,7 +142,7 @@ static int f32_tile(const GemmArgs& g) {
 static int tile_by_shape(bool f32, const GemmArgs& g) {
     const int f = forced_tile();
     if (f > 0) return f;
-    if (g.tile > TILE_AUTO && g.tile <= TILE_LAST) return g.tile;
+    if (g.tile > TILE_AUTO) return g.tile;
     if (f32) return f32_tile(g);  // both operands through LDS (the other kernels are bf16 only)
     const float c64 = tile_cost(64, g), c128 = tile_cost(128, g), c256 = tile_cost(256, g);
     if (decode_launch(g)) {
@@ -164,15 +164,19 @@ static int tile_by_shape(bool f32, const GemmArgs& g) {
     return c128 <= c256 ? TILE_PP_128 : TILE_PP_256;
 }
 
+static bool is_decode_tile(int tile) { return tile >= TILE_SKINNY_16 && tile <= TILE_DECODE_128; }
+
 // The tile a launch runs: tile_by_shape, or the tile that takes its place where
 // activation offsets do not fit the 32 bits (of 16 bytes each) that
 // gemm_pp.hpp and the weight streams of gemm_decode.hpp keep them in.  The
 // fp32 tiles address in 64 bits.
 static int launch_tile_number(bool f32, const GemmArgs& g) {
-    const int tile = tile_by_shape(f32, g);
-    if (f32 || g.T * (g.lda >> 3) <= INT32_MAX) return tile;
+    int tile = tile_by_shape(f32, g);
+    if (f32) return tile;
+    if (tile == TILE_192_128_64) tile = TILE_PP_256;
+    if (g.T * (g.lda >> 3) <= INT32_MAX) return tile;
     if (is_pp_tile(tile)) return TILE_MIX_256;
-    return tile >= TILE_SKINNY_16 ? TILE_DECODE_128 : tile;
+    return is_decode_tile(tile) ? TILE_DECODE_128 : tile;
 }
 
 bool gate_up_takes_norm(GemmArgs g) {
@@ -192,7 +196,7 @@ hipError_t launch_grouped_gemm(bool f32, int epi, GemmArgs g, hipStream_t s) {
         if (tile != TILE_SKINNY_16) tile = TILE_SKINNY_32;
         return launch_decode_bf16(tile, epi, g, s);
     }
-    if (!f32 && tile >= TILE_SKINNY_16) return launch_decode_bf16(tile, epi, g, s);
+    if (!f32 && is_decode_tile(tile)) return launch_decode_bf16(tile, epi, g, s);
     if (!f32 && is_pp_tile(tile)) {
         if (epi == EPI_GATE_UP_SILU) return launch_pp_bf16_gate_up(tile, g, s);
         if (epi == EPI_RESID_ADD) return launch_pp_bf16_resid(tile, g, s);
@@ -214,8 +218,15 @@ hipError_t launch_grouped_gemm(bool f32, int epi, GemmArgs g, hipStream_t s) {
 
 }  // namespace readme
 
-// Outside readme.h, for tests: the tile number (TileCfg) of a GEMM launch with
-// these sizes and the calling thread's override.
+// Outside readme.h, for tests: readme_set_gemm_tile for the kernels only the
+// automatic choice takes too, and the tile number (TileCfg) of a GEMM launch
+// with these sizes and the calling thread's override.
+extern "C" int32_t readme_internal_set_gemm_tile(int32_t tile) {
+    if (tile < readme::TILE_AUTO || tile > readme::TILE_PP_128) return README_ERR_ARG;
+    readme::t_forced_tile = tile;
+    return README_OK;
+}
+
 extern "C" int32_t readme_internal_gemm_tile(int32_t f32, int64_t T, int64_t N, int64_t K,
                                              int32_t E, int32_t shared_groups,
                                              int32_t m_tiles32, int32_t counts_order) {

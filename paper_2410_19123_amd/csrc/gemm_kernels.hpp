@@ -954,8 +954,11 @@ enum TileCfg {
     // Tiles of several heights in one launch, eight waves (two per SIMD) in
     // two opposite phases, both operands in LDS (bf16; see gemm_pp.hpp):
     TILE_PP_256 = 30,  // 256, 128, 64 rows
-    TILE_PP_128 = 31,  // 128, 64 rows
-    TILE_LAST = TILE_PP_128,  // the last that can be forced
+    // A number for launches of 192-row tiles, which TILE_PP_256 runs: it takes
+    // 0.56 to 1.07 of their time (108 GEMMs of 512 to 16384 tokens, d 1024 ..
+    // 8192; median 0.96), 128 and 64 rows up to 1.49.
+    TILE_192_128_64 = 31,
+    TILE_LAST = TILE_192_128_64,  // the last that can be forced
     // Weight streams for few tokens per expert (bf16; see gemm_decode.hpp).
     TILE_SKINNY_16 = 32,  // 32 rows x 16 columns
     TILE_SKINNY_32 = 33,  // 32 rows x 32 columns
@@ -965,6 +968,8 @@ enum TileCfg {
     TILE_F32_32x64_W2 = 36,     // 1x2 waves, 6 stages, 72 KB (2 per CU)
     TILE_F32_32x64_W2_S3 = 37,  // 1x2 waves, 3 stages, 36 KB (4 per CU)
     TILE_F32_64x64_W4 = 38,     // 2x2 waves, 3 stages, 48 KB (3 per CU)
+    // gemm_pp.hpp:
+    TILE_PP_128 = 39,  // 128, 64 rows
 };
 
 // Launches one tile configuration (instantiated per element type and

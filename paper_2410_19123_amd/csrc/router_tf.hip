@@ -683,7 +683,7 @@ hipError_t launch_attention(int64_t T, int H, int32_t R, const int32_t* pos, con
 // against 99 / 138 / 234.
 constexpr int kTileQkv = 30;     // TILE_PP_256
 constexpr int kTileNarrow = 13;  // TILE_BD_64x256
-constexpr int kTileGateUp = 31;  // TILE_PP_128
+constexpr int kTileGateUp = 39;  // TILE_PP_128
 
 // C[T][ldc] (+)= A[T][K] W^T over one group of all T rows, W a blocked bf16
 // [N][K] matrix.

@@ -8,6 +8,7 @@ import pytest
 # Tile numbers of the kernels no override reaches.
 SKINNY_16, SKINNY_32, SKINNY_64, DECODE_128 = 32, 33, 34, 35
 F32_32x64, F32_32x64_S3, F32_64x64 = 36, 37, 38
+PP_256, PP_128 = 30, 39
 INT32_MAX = 2 ** 31 - 1
 
 
@@ -36,7 +37,7 @@ def test_bf16_past_32_bit_offsets(tile):
     """Tiles whose activation offsets are 32-bit give way to 64-bit ones."""
     T = 4 << 20
     assert T * 8192 // 8 > INT32_MAX
-    assert tile(T // 8, 1024, 8192, 8) == 30
+    assert tile(T // 8, 1024, 8192, 8) == PP_256
     assert tile(T, 1024, 8192, 8) == 24
 
 
@@ -66,7 +67,7 @@ def test_a_row_group_is_at_least_one_tile(tile):
     """Many experts whose rows fill a small part of a tall tile: the estimate
     counts a tile for each, not the rows' share of one."""
     for E, N, K in ((64, 1024, 1024), (32, 2816, 4096), (16, 7168, 8192)):
-        assert tile(E * 40, N, K, E) != 30
+        assert tile(E * 40, N, K, E) != PP_256
 
 
 @pytest.mark.parametrize("T,E", [(32, 16), (200, 8), (500, 64), (3, 3)])
@@ -80,3 +81,15 @@ def test_32x128_decode_tile_of_layers_and_stacks(tile, T, E):
     assert layer == (27 if stack == DECODE_128 else stack)
     for m32 in range(1, min(E, T) + 1):
         assert tile(T, N, K, E, stack=True, m32=m32) in streams + (DECODE_128,)
+
+
+def test_tile_31_runs_the_tallest_tiles(tile):
+    """A stored choice of 31 (made when it meant 192-row tiles) keeps a launch of
+    tall tiles at every size."""
+    from paper_2410_19123_amd import _lib
+    try:
+        for forced in (30, 31):
+            _lib.readme_set_gemm_tile(forced)
+            assert tile(8192, 7168, 8192, 8) == tile(512, 1024, 1024, 8) == PP_256
+    finally:
+        _lib.readme_set_gemm_tile(0)
