@@ -340,3 +340,13 @@ def test_fused_kernels_every_stage(lengths, F, E):
     shape = wl.RouterShape(D=512, F=F, V=1000, E=E)
     w, tokens, ro, ids, logits, g = _forward(shape, lengths, 31, bad_tokens=True)
     _stage_checks(w, tokens, ro, ids, logits, g)
+
+
+def test_fused_kernels_many_requests():
+    """More offsets than the fused head stages in LDS: positions searched in
+    global memory."""
+    lengths = [1, 0, 2, 1, 2] * 1000
+    assert len(lengths) + 1 > 4096 and sum(lengths) >= 1800 + 64 * 7 // 5
+    shape = wl.RouterShape(D=512, F=64, V=1000, E=8)
+    w, tokens, ro, ids, logits, g = _forward(shape, lengths, 37)
+    _stage_checks(w, tokens, ro, ids, logits, g)
