@@ -415,66 +415,52 @@ struct Epilogue {
 // waves put their fp32 sums into a row-major LDS tile, then all threads form
 // h = silu(g) * u for 16 bytes of neurons at a time and store whole output
 // rows with 16-byte stores (same fp32 arithmetic as Epilogue, so the same
-// bits).  A tall tile of many waves goes through LDS CH 32-row blocks at a time.
-template <int TM, int NW, bool F32 = false, int WGM = 1>
+// bits).  WGM rows of NW waves, each wave one 32 x 32 block.
+template <int NW, bool F32 = false, int WGM = 1>
 struct EpiloguePairWaves {
-    static_assert(WGM == 1 || TM == 1, "one block per wave row");
     using OT = std::conditional_t<F32, float, uint16_t>;
     static constexpr int PC = 16 / (int)sizeof(OT);          // neurons per 16-byte piece
     static constexpr int LDF = NW * 32 + 4;                  // fp32 row pitch
-    // 32-row blocks staged at once: the most (dividing TM) that fit 72 KB.
-    static constexpr int chunk() {
-        int c = TM;
-        while (c > 1 && (TM % c != 0 || c * 32 * LDF * 4 > 73728)) --c;
-        return c;
-    }
-    static constexpr int CH = chunk();
-    static constexpr int LDS_BYTES = WGM * CH * 32 * LDF * 4;
+    static constexpr int LDS_BYTES = WGM * 32 * LDF * 4;
     static constexpr int PER_ROW = NW * 16 / PC;             // pieces per row
     static_assert(NW % 2 == 0, "gate and up waves come in pairs");
 
-    __device__ static void run(const GemmArgs& g, const f32x16 (&acc)[TM][1], int wm, int wn,
+    __device__ static void run(const GemmArgs& g, const f32x16 (&acc)[1][1], int wm, int wn,
                                int64_t n0, int rows, int64_t m0, const int32_t* crow,
                                void* lds_raw, int tid, int nthreads) {
         float* L = reinterpret_cast<float*>(lds_raw);
         const int lane = tid & 63;
         const int64_t oc0 = n0 / 2, n_out = g.N / 2;
+        __syncthreads();  // K-loop LDS reads are done
 #pragma unroll
-        for (int c0 = 0; c0 < TM; c0 += CH) {
-            __syncthreads();  // LDS free (K loop or the previous block done)
+        for (int r = 0; r < 16; ++r) {
+            const int lr = wm * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+            L[lr * LDF + wn * 32 + (lane & 31)] = acc[0][0][r];
+        }
+        __syncthreads();
+        for (int u = tid; u < WGM * 32 * PER_ROW; u += nthreads) {
+            const int rt = u / PER_ROW, pc = u - rt * PER_ROW;  // row in the tile
+            if (rt >= rows) continue;
+            const int64_t col = oc0 + (int64_t)pc * PC;
+            if (col >= n_out) continue;
+            const int64_t grow = g.c_rows ? (int64_t)crow[rt] : m0 + rt;
+            if (grow < 0 || grow >= g.T) continue;
+            const int ng = pc / (32 / PC), w0 = (pc % (32 / PC)) * PC;  // neuron group, first neuron in it
+            const float* gt = L + rt * LDF + (2 * ng) * 32 + w0;
+            const float* up = L + rt * LDF + (2 * ng + 1) * 32 + w0;
+            uint32_t packed[4];
 #pragma unroll
-            for (int i = 0; i < CH; ++i)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int lr = (wm + i) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                    L[lr * LDF + wn * 32 + (lane & 31)] = acc[c0 + i][0][r];
+            for (int k = 0; k < 4; ++k) {
+                if constexpr (F32) {
+                    packed[k] = __float_as_uint(silu_f32(gt[k]) * up[k]);
+                    continue;
                 }
-            __syncthreads();
-            for (int u = tid; u < WGM * CH * 32 * PER_ROW; u += nthreads) {
-                const int rl = u / PER_ROW, pc = u - rl * PER_ROW;  // row in the block
-                const int rt = c0 * 32 + rl;                        // row in the tile
-                if (rt >= rows) continue;
-                const int64_t col = oc0 + (int64_t)pc * PC;
-                if (col >= n_out) continue;
-                const int64_t grow = g.c_rows ? (int64_t)crow[rt] : m0 + rt;
-                if (grow < 0 || grow >= g.T) continue;
-                const int ng = pc / (32 / PC), w0 = (pc % (32 / PC)) * PC;  // neuron group, first neuron in it
-                const float* gt = L + rl * LDF + (2 * ng) * 32 + w0;
-                const float* up = L + rl * LDF + (2 * ng + 1) * 32 + w0;
-                uint32_t packed[4];
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    if constexpr (F32) {
-                        packed[k] = __float_as_uint(silu_f32(gt[k]) * up[k]);
-                        continue;
-                    }
-                    const uint32_t lo = f32_to_bf16(silu_f32(gt[2 * k]) * up[2 * k]);
-                    const uint32_t hi = f32_to_bf16(silu_f32(gt[2 * k + 1]) * up[2 * k + 1]);
-                    packed[k] = lo | (hi << 16);
-                }
-                const u32x4 v = {packed[0], packed[1], packed[2], packed[3]};
-                *reinterpret_cast<u32x4*>(reinterpret_cast<OT*>(g.C) + grow * g.ldc + col) = v;
+                const uint32_t lo = f32_to_bf16(silu_f32(gt[2 * k]) * up[2 * k]);
+                const uint32_t hi = f32_to_bf16(silu_f32(gt[2 * k + 1]) * up[2 * k + 1]);
+                packed[k] = lo | (hi << 16);
             }
+            const u32x4 v = {packed[0], packed[1], packed[2], packed[3]};
+            *reinterpret_cast<u32x4*>(reinterpret_cast<OT*>(g.C) + grow * g.ldc + col) = v;
         }
     }
 };
@@ -500,11 +486,11 @@ __global__ __launch_bounds__(WGM* WGN * 64) void k_grouped_gemm(GemmArgs args) {
     static_assert(A_INS * RPI * NW == BM && B_INS * RPI * NW == BN, "DMA split");
     // Waves of one 32-column group: gate and up meet across two of them.
     constexpr bool PAIR = EPI == EPI_GATE_UP_SILU && TN == 1;
-    static_assert(EPI != EPI_GATE_UP_SILU || (PAIR || WN % 64 == 0), "gate/up pairs");
+    static_assert(EPI != EPI_GATE_UP_SILU || (PAIR && TM == 1) || WN % 64 == 0, "gate/up pairs");
     static_assert(NSTAGE >= 2 && LPS * (NSTAGE - 2) < 64, "stages");
 
     constexpr int BUDGET = NSTAGE * STAGE * 16 > 73728 ? NSTAGE * STAGE * 16 : 73728;
-    using Epi = std::conditional_t<PAIR, EpiloguePairWaves<PAIR ? TM : 1, PAIR ? WGN : 2, F32, WGM>,
+    using Epi = std::conditional_t<PAIR, EpiloguePairWaves<PAIR ? WGN : 2, F32, WGM>,
                                    Epilogue<TM, TN, WGM, WGN, F32, EPI, BUDGET>>;
     constexpr int LDS_SLOTS = NSTAGE * STAGE > Epi::LDS_BYTES / 16 ? NSTAGE * STAGE : Epi::LDS_BYTES / 16;
     __shared__ u32x4 lds[LDS_SLOTS];
@@ -686,7 +672,7 @@ struct BdTile {
     static constexpr int STAGE = BM * CPR;  // u32x4 slots per LDS buffer
     // One 32-column group per wave: gate and up meet across waves.
     using Epi = std::conditional_t<(EPI == EPI_GATE_UP_SILU && TN == 1 && !F32),
-                                   EpiloguePairWaves<TM, NW>,
+                                   EpiloguePairWaves<NW>,
                                    Epilogue<TM, TN, 1, NW, F32, EPI, 73728>>;
     static constexpr int LDS_SLOTS =
         2 * STAGE > Epi::LDS_BYTES / 16 ? 2 * STAGE : Epi::LDS_BYTES / 16;
@@ -701,7 +687,8 @@ struct BdTile {
     constexpr int ESZ = F32 ? 4 : 2;
     constexpr int A_INS = BM / 8 / NW;    // activation loads per wave per K-step
     static_assert(BM % 32 == 0 && A_INS * 8 * NW == BM, "activation split");
-    static_assert(EPI != EPI_GATE_UP_SILU || TN % 2 == 0 || (TN == 1 && NW % 2 == 0 && !F32),
+    static_assert(EPI != EPI_GATE_UP_SILU || TN % 2 == 0 ||
+                      (TN == 1 && TM == 1 && NW % 2 == 0 && !F32),
                   "gate/up pairs");
     static_assert(S >= 2, "stages");
 
