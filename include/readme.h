@@ -164,7 +164,7 @@ int64_t readme_padded_intermediate(int64_t I);
  * readme_set_gemm_tile -- force one workgroup tile for the grouped GEMMs that
  * the CALLING HOST THREAD launches (thread-local: other threads keep their
  * own setting, 0 at start), for tuning and for testing every configuration.
- *   0 = automatic (by tokens per expert, the default)
+ *   0 = automatic (by T, E and the GEMM's size, the default)
  *   both operands staged in LDS:
  *     1 = 256x256, 2 = 256x128, 3 = 128x128, 4 = 128x256, 5 = 64x128,
  *     6 = 32x128, 7 = 32x64 (deep pipeline), 8 = 32x128 (deep pipeline),
@@ -182,7 +182,11 @@ int64_t readme_padded_intermediate(int64_t I);
  *     weights in registers), 30 = 256/128/64 (eight waves in two opposite
  *     phases, both operands in LDS), 31 = the same as 30
  *   (rows of tokens x columns of outputs)
- * Results do not depend on the tile beyond fp32 summation order.  Returns
+ * Results do not depend on the tile beyond fp32 summation order.  The
+ * automatic choice follows from the sizes of a call alone (and, in a stack,
+ * never changes with the counts), so equal calls give equal bits; a token's
+ * bits may differ between calls of other T, E, d or I, where K is added in
+ * another order.  Returns
  * README_ERR_ARG for any other value.  readme_get_gemm_tile returns the
  * calling thread's current setting.
  */

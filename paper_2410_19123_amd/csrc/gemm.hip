@@ -46,10 +46,11 @@ static float row_tiles(int height, const GemmArgs& g) {
 // that a round costs more than its share because rounds end ragged.  The
 // constants fit a sweep of all tiles on MI355X over 2627 layers (d 512 .. 8192,
 // I 256 .. 3584, 1 .. 128 experts, 1 .. 1024 tokens per expert; uniform, Zipf
-// and one-expert loads; 1.3% of the 5254 GEMMs run more than 4% longer than
-// on the tiles that were chosen by tokens per expert alone, 8.6% without the
-// tile per row group and with other constants); us of gate/up, uniform load,
-// 32x128 / 64x256 / 128 rows / 256 rows:
+// and one-expert loads).  Against the register-streamed tiles chosen by tokens
+// per expert alone, the 5254 GEMMs take 29.3 us at the geometric mean, 35.5
+// there; 1.4% take over 4% longer (up to 1.45 times, 192 rows per expert, where
+// the split decides), 8.3% did without the tile per row group and with other
+// constants.  us of gate/up, uniform load, 32x128 / 64x256 / 128 rows / 256 rows:
 //   d 6400, I 955, 32 experts of 48 tokens      163 / 198 / 195 / 196
 //   d 1024, I 512, 128 experts of 64             73 /  59 /  76 /  78
 //   d 4096, I 1376, 8 experts of 128             78 /  56 /  66 /  75
@@ -92,6 +93,11 @@ static float decode_m_tiles(const GemmArgs& g) {
 // activation rows (16 rows per 16-token tile, all of them by every
 // workgroup).  128 columns: the tile whose waves share the rows through LDS;
 // more than one fits a CU, so a second round costs less than a whole one.
+// This ranks the widths, no more: 46 bytes per ns and CU is past what HBM
+// delivers to all 256 (23).  Holding each width to the stream's time as well (5.0
+// or 5.6 TB/s) made the choice no better over the 2052 launches of under 28 rows
+// per expert in the sweep above (geometric mean 23.10 us, held 23.17 and 23.11;
+// the best width of each 22.3).
 static float decode_cost(int cols, const GemmArgs& g, float m) {
     const float n = m * (float)ceil_div(g.N, (int64_t)cols) / 256.0f;
     const float rows = cols == 128 || (float)g.T > 16.0f * m ? 32.0f : 16.0f;

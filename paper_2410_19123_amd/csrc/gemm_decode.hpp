@@ -1,7 +1,8 @@
 // Grouped GEMM for few tokens per expert (decode, bf16): weight streams.
 //
 // What bounds it: bytes.  One Llama-7B-shaped expert's gate/up is 23 MB, 4 us
-// at the card's rate when all 256 CUs pull (each takes about 46 bytes per ns,
+// at the card's read rate of 5.8 TB/s (23 bytes per ns and CU with all 256
+// pulling; one of few pulls up to about 46, activation rows from L2 included,
 // however its waves are arranged), so what matters is how many workgroups a
 // launch has and how evenly the CUs are loaded.  A 32 x 128 tile gives one
 // expert 22 workgroups (gate/up) and 32 (down): 24.5 and 11.8 us for one
@@ -21,7 +22,7 @@
 // 43.4 -> 34.4, 16 on 5 (counts known) 46.2 -> 41.2.
 //
 // k_decode: 32 x 128, token rows shared through LDS, for more experts than
-// that: 64 tokens on 7 experts move 5.3 TB/s in gate/up (32.6 us with its
+// that in a stack (gemm.hip says which tile a layer takes instead): 64 tokens on 7 experts move 5.3 TB/s in gate/up (32.6 us with its
 // launch, 28.2 at 5.6 TB/s).
 //
 // Both add K in the same order -- DECODE_SPLITS ranges, each from zero, then

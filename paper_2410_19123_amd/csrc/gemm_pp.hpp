@@ -44,8 +44,10 @@
 // second, so a lane's four accumulator values are four consecutive output
 // columns of one token; one lane exchange (v_permlane16_swap) makes that
 // eight bf16 columns and the epilogue stores 16 bytes per lane straight from
-// registers, with no LDS and no barrier.  The sums equal the other tiles' bit
-// for bit.
+// registers, with no LDS and no barrier.  The sums equal those of the other
+// tiles that run straight through K (the LDS and the register-streamed ones, the
+// residual first where it is added) bit for bit; the decode tiles add K in four
+// ranges (gemm_decode.hpp).
 #pragma once
 
 #include "gemm_mix.hpp"

@@ -25,6 +25,11 @@
 // 16384 195 -> 165; at F = 1536, 4096 tokens 107 -> 104, 8192 157 -> 123; below
 // that they are the faster form (2048 tokens: 68 against 74).  Starting each
 // workgroup on another of q, k and v made no difference.
+//
+// D = 512, the width the block is specified with, is compiled in: a wave's two
+// groups of 32 columns, the row of 64 16-byte chunks (one per lane) and the fp32
+// residual in registers are sized for it.  Other widths keep the nine launches;
+// what two kernels would give them has not been measured.
 #include "gemm_kernels.hpp"
 #include "router_common.hpp"
 

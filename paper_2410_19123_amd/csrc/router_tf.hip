@@ -678,9 +678,11 @@ hipError_t launch_attention(int64_t T, int H, int32_t R, const int32_t* pos, con
 // the fused kernels do not run and T * D is at least 4 M: q|k|v on 256-row
 // tiles, o and down (N = D) on 64 x 256, gate/up on 128 rows.  Below that the
 // automatic choice is the faster one (whole block, us, these tiles against
-// it): D = 256, F = 256, 2048 / 8192 / 16384 tokens 74 / 97 / 121 against 52 /
-// 87 / 132; D = 1024, F = 256, 2048 / 4096 / 8192 tokens 120 / 136 / 210
-// against 99 / 138 / 234.
+// it): D = 256, F = 256, 2048 / 8192 / 16384 tokens 74 / 96 / 121 against 53 /
+// 86 / 124; D = 1024, F = 256, 2048 / 4096 / 8192 tokens 117 / 135 / 207
+// against 96 / 135 / 224.  It is also the faster one for many tokens and an MLP
+// wider than D, by up to 15% (D = 1024, F = 2816, 32768 tokens: 1332 against
+// 1156); the line does not follow that.
 constexpr int kTileQkv = 30;     // TILE_PP_256
 constexpr int kTileNarrow = 13;  // TILE_BD_64x256
 constexpr int kTileGateUp = 39;  // TILE_PP_128
