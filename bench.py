@@ -351,26 +351,26 @@ class Path:
 # reads exactly 1 GiB, factor 1).  Valid only for the sources the counters were taken
 # with: each entry carries their sha256 and is dropped (traffic null) once any of
 # them changes.
-_GEMM_SOURCES = ["csrc/gemm_kernels.hpp", "csrc/gemm_mix.hpp", "csrc/gemm.hip",
-                 "csrc/gemm_mix_gate_up.hip", "csrc/common.hpp", "csrc/internal.hpp",
-                 "csrc/pack.hip", "workloads.py"]
-_STACK_SOURCES = ["csrc/gemm_kernels.hpp", "csrc/gemm.hip", "csrc/gemm_bf16_gate_up.hip",
-                  "csrc/gemm_bf16_resid.hip", "csrc/norm.hip", "csrc/abi.hip",
-                  "csrc/common.hpp", "csrc/internal.hpp", "csrc/pack.hip", "workloads.py"]
+_GEMM_SOURCES = ["csrc/gemm_kernels.hpp", "csrc/gemm_mix.hpp", "csrc/gemm_pp.hpp",
+                 "csrc/gemm_pp_gate_up.hip", "csrc/gemm.hip", "csrc/common.hpp",
+                 "csrc/internal.hpp", "csrc/pack.hip", "workloads.py"]
+_STACK_SOURCES = ["csrc/gemm_kernels.hpp", "csrc/gemm_decode.hpp", "csrc/gemm_decode.hip",
+                  "csrc/gemm.hip", "csrc/norm.hip", "csrc/abi.hip", "csrc/common.hpp",
+                  "csrc/internal.hpp", "csrc/pack.hip", "workloads.py"]
 TRAFFIC = {
     # workload: (sources, their sha256, read bytes, written bytes) per launch of the
     # dominant call: the gate/up GEMM (profiles/traffic_gate_up_wide_requests.md,
     # profiles/traffic_gate_up_prefill_skew16.md), or the whole 32-layer stack
     # (profiles/traffic_stack_llama7b_decode32.md)
     "wide_requests": (_GEMM_SOURCES,
-                      "f2e5982ee17904e80e59c9f86a5a9dcabc2500a967656b365c81d094c306a252",
-                      2255728392, 58720256),
+                      "d024d7d4161d5e02c2397d3b1d234ae573f43a847a721d769e1a1697ca3117af",
+                      2370620469, 58720268),
     "prefill_skew16": (_GEMM_SOURCES,
-                       "f2e5982ee17904e80e59c9f86a5a9dcabc2500a967656b365c81d094c306a252",
-                       609159683, 23068672),
+                       "d024d7d4161d5e02c2397d3b1d234ae573f43a847a721d769e1a1697ca3117af",
+                       610605423, 23068675),
     "llama7b_decode32": (_STACK_SOURCES,
-                         "600e4d122b11f65a2481f6be9870ec15ad14c9dfec5c1e1f0542ef625b3bea90",
-                         7873977716, 56098816),
+                         "00ae397483586b8adeaa6259eee00508863aa2fa4a252d304f233aa0fdf68b04",
+                         7875373856, 56098816),
 }
 
 

@@ -115,3 +115,22 @@ def test_router_flops():
     f = bench.router_flops(shape, [32] * 256)
     assert f == 8192 * per_token + 256 * 528 * 4 * 128 * 4
     assert f / 1e9 == pytest.approx(30.41, abs=0.01)
+
+
+def test_traffic_sources_hold_the_kernels_that_run():
+    """The sources of each entry include those of the tile its workload's
+    gate/up takes (and gemm.hip, which chooses it)."""
+    import ctypes
+    import os
+    from paper_2410_19123_amd import _lib
+    if not os.path.exists(_lib.LIB_PATH):
+        pytest.skip("libreadme.so not built")
+    fn = _lib.load().readme_internal_gemm_tile
+    fn.restype = ctypes.c_int32
+    fn.argtypes = [ctypes.c_int32] + [ctypes.c_int64] * 3 + [ctypes.c_int32] * 4
+    files = {30: "csrc/gemm_pp.hpp", 39: "csrc/gemm_pp.hpp", 35: "csrc/gemm_decode.hpp"}
+    for name, (sources, _, _, _) in bench.TRAFFIC.items():
+        w = wl.WORKLOADS[name]
+        Ip = (w.I + 63) // 64 * 64
+        tile = fn(0, w.T, 2 * Ip, w.d, w.E, 0, 0, w.layers > 1)
+        assert files[tile] in sources and "csrc/gemm.hip" in sources, (name, tile)
