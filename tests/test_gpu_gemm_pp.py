@@ -1,4 +1,4 @@
-"""The two-phase grouped GEMM (tiles 30 and 31) at the sizes where its loop,
+"""The two-phase grouped GEMM (tiles 30 and 31, one launch) at the sizes where its loop,
 its row classes and its row maps can go wrong, against the oracle."""
 import numpy as np
 import pytest
