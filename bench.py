@@ -363,13 +363,13 @@ TRAFFIC = {
     # profiles/traffic_gate_up_prefill_skew16.md), or the whole 32-layer stack
     # (profiles/traffic_stack_llama7b_decode32.md)
     "wide_requests": (_GEMM_SOURCES,
-                      "d024d7d4161d5e02c2397d3b1d234ae573f43a847a721d769e1a1697ca3117af",
+                      "eb360134d14a65267e9ab26150ed9e653bc777b414cce289e968d11007ef77b6",
                       2370620469, 58720268),
     "prefill_skew16": (_GEMM_SOURCES,
-                       "d024d7d4161d5e02c2397d3b1d234ae573f43a847a721d769e1a1697ca3117af",
+                       "eb360134d14a65267e9ab26150ed9e653bc777b414cce289e968d11007ef77b6",
                        610605423, 23068675),
     "llama7b_decode32": (_STACK_SOURCES,
-                         "00ae397483586b8adeaa6259eee00508863aa2fa4a252d304f233aa0fdf68b04",
+                         "cec68098307e904cd62067ecde548b7f2dadd67ce421becbbd72a61b48e42786",
                          7875373856, 56098816),
 }
 

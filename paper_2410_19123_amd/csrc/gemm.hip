@@ -32,25 +32,28 @@ static float active_experts(const GemmArgs& g) {
 }
 
 // Estimated row tiles of `height` rows: the host does not know the split over
-// experts, so each row group is taken to end in half a tile of padding, and
-// each that has rows at all has a tile.
+// experts, so each row group is taken to end in about half a tile of padding
+// and to have at least one tile.
 static float row_tiles(int height, const GemmArgs& g) {
     const float groups = active_experts(g) + (float)g.shared_groups;
-    const float full = (float)group_rows(g) / height + 0.5f * groups;
+    const float full = (float)group_rows(g) / height + (height == 32 ? 0.52f : 0.47f) * groups;
     return full > groups ? full : groups;
 }
 
-// Estimated time (us, up to a common offset) of one launch on tiles of
-// `height` rows x 256 columns.  A tile costs a fixed start and end plus a time
-// per 64-element K-step; up to 256 tiles run at once (one per CU), and past
-// that a round costs more than its share because rounds end ragged.  The
-// constants fit a sweep of all tiles on MI355X over 2627 layers (d 512 .. 8192,
-// I 256 .. 3584, 1 .. 128 experts, 1 .. 1024 tokens per expert; uniform, Zipf
-// and one-expert loads).  Against the register-streamed tiles chosen by tokens
-// per expert alone, the 5254 GEMMs take 29.3 us at the geometric mean, 35.5
-// there; 1.4% take over 4% longer (up to 1.45 times, 192 rows per expert, where
-// the split decides), 8.3% did without the tile per row group and with other
-// constants.  us of gate/up, uniform load, 32x128 / 64x256 / 128 rows / 256 rows:
+// Estimated time of one launch on tiles of `height` rows x 256 columns, to
+// compare heights (not in us).  A tile costs a start and end that grow with its
+// rows and a time per 64-element K-step that hardly does (the CU's load path);
+// 256 tiles run at once (one per CU), a launch of just 256 no longer does (the
+// tiles are dealt to the XCDs in whole numbers), and past that a round costs
+// more than its share because rounds end ragged.  The constants fit a sweep of
+// all tiles on MI355X over 4837 layers (d 512 .. 8192, I 64 .. 4096, 1 .. 128
+// experts, 1 .. 4096 tokens per expert; uniform, Zipf and one-expert loads), for
+// the time and against launches longer than on the tiles chosen before.  Over
+// 11254 GEMMs of such layers, geometric mean: 28.1 us on the register-streamed
+// tiles by tokens per expert alone, 22.2 by an estimate without a tile per row
+// group and a start and end per decode tile, 22.0 by this one; 7.0% and 1.9% of
+// the launches take over 4% longer than on the first, 0.7% than by the second.
+// us of gate/up, uniform load, 32x128 / 64x256 / 128 rows / 256 rows:
 //   d 6400, I 955, 32 experts of 48 tokens      163 / 198 / 195 / 196
 //   d 1024, I 512, 128 experts of 64             73 /  59 /  76 /  78
 //   d 4096, I 1376, 8 experts of 128             78 /  56 /  66 /  75
@@ -58,21 +61,22 @@ static float row_tiles(int height, const GemmArgs& g) {
 static float tile_cost(int height, const GemmArgs& g) {
     const float nk = (float)g.K / 64.0f;
     const float tiles = row_tiles(height, g) * ceil_div(g.N, 256) / 256.0f;
-    const float rounds = tiles <= 1.0f ? 1.0f : tiles + 0.25f;
-    if (height == 64) return rounds * (5.0f + 0.78f * nk);
-    if (height == 128) return rounds * (6.5f + 0.95f * nk);
-    return rounds * (10.0f + 0.97f * nk);
+    const float rounds = tiles <= 0.985f ? 1.0f : (tiles > 1.0f ? tiles : 1.0f) + 0.29f;
+    if (height == 64) return rounds * (4.2f + 0.86f * nk);
+    if (height == 128) return rounds * (5.6f + 0.905f * nk);
+    return rounds * (7.2f + 0.895f * nk);
 }
 
 // Whether the launch is a decode launch: by its sizes alone, never by the
-// counts, since the summation order follows from it.  Under 28 rows per group
-// always: a taller tile is then more padding than rows, and the weights it
-// streams come in with fewer workgroups (64 x 256 against 32 x 128, 16 to 64
-// experts: 1.02 to 1.10 times as long at 8 rows, 0.89 to 0.97 at 32).
+// counts, since the summation order follows from it.  Under 8 rows per group
+// always: a taller tile is then mostly padding, and the weights it streams come
+// in with fewer workgroups (64 x 256 against 32 x 128, 16 to 64 experts: 1.02
+// to 1.10 times as long at 8 rows, 0.89 to 0.97 at 32).  Else where the time of
+// its 32 x 128 tiles, many of them on the chip at once, is the least.
 static bool decode_launch(const GemmArgs& g) {
-    if (group_rows(g) < 28 * row_groups(g)) return true;
-    const float t = 0.42f * row_tiles(32, g) * ceil_div(g.N, 128) / 256.0f;
-    const float cost = 3.0f + (float)g.K / 64.0f * (t > 0.5f ? t : 0.5f);
+    if (group_rows(g) < 8 * row_groups(g)) return true;
+    const float cost = row_tiles(32, g) * ceil_div(g.N, 128) / 256.0f *
+                       (0.94f + 0.475f * (float)g.K / 64.0f);
     return cost <= tile_cost(64, g) && cost <= tile_cost(128, g) && cost <= tile_cost(256, g);
 }
 
@@ -95,8 +99,8 @@ static float decode_m_tiles(const GemmArgs& g) {
 // more than one fits a CU, so a second round costs less than a whole one.
 // This ranks the widths, no more: 46 bytes per ns and CU is past what HBM
 // delivers to all 256 (23).  Holding each width to the stream's time as well (5.0
-// or 5.6 TB/s) made the choice no better over the 2052 launches of under 28 rows
-// per expert in the sweep above (geometric mean 23.10 us, held 23.17 and 23.11;
+// or 5.6 TB/s) made the choice no better over 2052 launches of under 28 rows per
+// expert (I 256 .. 3584; geometric mean 23.10 us, held 23.17 and 23.11;
 // the best width of each 22.3).
 static float decode_cost(int cols, const GemmArgs& g, float m) {
     const float n = m * (float)ceil_div(g.N, (int64_t)cols) / 256.0f;
@@ -142,7 +146,7 @@ static int f32_tile(const GemmArgs& g) {
 // the faster one of 4314 GEMMs by 1 to 2% at the median, by 7 to 16% (1 to 3 us)
 // where fewer than 64 tiles have rows, so that a CU has one workgroup that waits
 // for its own loads, and K is 1024 or more; with K below that it is 3% (0.2 us)
-// slower there.  Else 64 x 256 (four waves) or one of the
+// slower there and not taken.  Else 64 x 256 (four waves) or one of the
 // mixed-height launches of gemm_pp.hpp, whose tall tiles are the fastest per
 // flop.
 static int tile_by_shape(bool f32, const GemmArgs& g) {
@@ -163,7 +167,7 @@ static int tile_by_shape(bool f32, const GemmArgs& g) {
                 best = i;
             }
         }
-        if (best == 0 && !g.counts_order) return TILE_BD_32x128_W4;
+        if (best == 0 && !g.counts_order && g.K >= 1024) return TILE_BD_32x128_W4;
         return tile[best];
     }
     if (c64 <= c128 && c64 <= c256) return TILE_BD_64x256;
