@@ -364,13 +364,13 @@ TRAFFIC = {
     # (profiles/traffic_stack_llama7b_decode32.md)
     "wide_requests": (_GEMM_SOURCES,
                       "eb360134d14a65267e9ab26150ed9e653bc777b414cce289e968d11007ef77b6",
-                      2370620469, 58720268),
+                      2369895211, 58720265),
     "prefill_skew16": (_GEMM_SOURCES,
                        "eb360134d14a65267e9ab26150ed9e653bc777b414cce289e968d11007ef77b6",
-                       610605423, 23068675),
+                       610736269, 23068672),
     "llama7b_decode32": (_STACK_SOURCES,
                          "cec68098307e904cd62067ecde548b7f2dadd67ce421becbbd72a61b48e42786",
-                         7875373856, 56098816),
+                         7875365792, 56098816),
 }
 
 
